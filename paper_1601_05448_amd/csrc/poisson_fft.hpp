@@ -156,8 +156,50 @@ __device__ __forceinline__ void dft(cpx<T>* v) {
     if constexpr (R == 2) dft2(v);
     else if constexpr (R == 3) dft3(v);
     else if constexpr (R == 4) dft4(v);
+    else if constexpr (R == 6) dft6(v);
     else if constexpr (R == 8) dft8(v);
-    else dft16(v);
+    else if constexpr (R == 12) dft12(v);
+    else if constexpr (R == 16) dft16(v);
+    else static_assert(R == 1, "no such radix");
+}
+
+// 6 = 2 x 3 and 12 = 4 x 3 with coprime factors (Good, Thomas): with the inputs
+// taken at n = 3 n1 + (N/3) n2 and the outputs left at the k of residues k1 mod
+// N/3 and k2 mod 3, no twiddles stand between the two passes.
+template <typename T>
+__device__ __forceinline__ void dft6(cpx<T>* v) {
+    cpx<T> o[6];
+#pragma unroll
+    for (int k1 = 0; k1 < 2; ++k1) {
+        cpx<T> c[3];
+#pragma unroll
+        for (int n2 = 0; n2 < 3; ++n2) {
+            const cpx<T> a = v[(2 * n2) % 6], b = v[(3 + 2 * n2) % 6];
+            c[n2] = k1 == 0 ? cadd(a, b) : csub(a, b);
+        }
+        dft3(c);
+#pragma unroll
+        for (int k2 = 0; k2 < 3; ++k2) o[(3 * k1 + 4 * k2) % 6] = c[k2];
+    }
+#pragma unroll
+    for (int r = 0; r < 6; ++r) v[r] = o[r];
+}
+
+template <typename T>
+__device__ __forceinline__ void dft12(cpx<T>* v) {
+    cpx<T> o[12];
+#pragma unroll
+    for (int n2 = 0; n2 < 3; ++n2)
+        dft4v(v[(4 * n2) % 12], v[(3 + 4 * n2) % 12], v[(6 + 4 * n2) % 12], v[(9 + 4 * n2) % 12]);
+#pragma unroll
+    for (int k1 = 0; k1 < 4; ++k1) {
+        cpx<T> c[3] = {v[(3 * k1) % 12], v[(3 * k1 + 4) % 12], v[(3 * k1 + 8) % 12]};
+        dft3(c);
+#pragma unroll
+        for (int k2 = 0; k2 < 3; ++k2) o[(9 * k1 + 4 * k2) % 12] = c[k2];
+    }
+#pragma unroll
+    for (int r = 0; r < 12; ++r) v[r] = o[r];
 }
 
 // ---- line geometry ------------------------------------------------------------
@@ -265,6 +307,171 @@ __device__ __forceinline__ void fft_block_lines(cpx<T>* lds, const cpx<T>* tw) {
     const int t = threadIdx.x % C::TT;
     fft_stages<T, N, 1, C::TT>(lds + line * C::LS, t, tw);
 }
+
+// ---- transforms whose first and last stages stay in registers ---------------------
+// The same Stockham stages, with radices R[0] R[1] R[2] = N chosen so that a line
+// of TT = N / R[0] threads starts from registers: thread t enters with its E =
+// R[0] values x[t + a TT], the inputs of its one butterfly of the first stage,
+// and leaves with the outputs of its butterflies of the last stage, X[k] at
+// k = t + u TT + r N/R.  A two-stage line passes LDS once (three stages: twice)
+// where stages that start and end in LDS pass it N_stages + 1 times.
+constexpr int plan_radix(int n, int s) {
+    int r[3] = {0, 1, 1};
+    switch (n) {
+        case 4: case 6: case 8: case 12: r[0] = n; break;
+        case 16: r[0] = 4; r[1] = 4; break;
+        case 24: r[0] = 6; r[1] = 4; break;
+        case 32: r[0] = 8; r[1] = 4; break;
+        case 48: r[0] = 12; r[1] = 4; break;
+        case 64: r[0] = 8; r[1] = 8; break;
+        case 96: r[0] = 12; r[1] = 8; break;
+        case 128: r[0] = 16; r[1] = 8; break;
+        case 192: r[0] = 12; r[1] = 16; break;
+        case 256: r[0] = 16; r[1] = 16; break;
+        case 384: r[0] = 12; r[1] = 8; r[2] = 4; break;
+        case 512: r[0] = 8; r[1] = 8; r[2] = 8; break;
+        case 768: r[0] = 12; r[1] = 8; r[2] = 8; break;
+        case 1024: r[0] = 16; r[1] = 8; r[2] = 8; break;
+        default: break;
+    }
+    return r[s];
+}
+
+template <int N>
+struct FftPlan {
+    static constexpr int R0 = plan_radix(N, 0), R1 = plan_radix(N, 1), R2 = plan_radix(N, 2);
+    static_assert(R0 * R1 * R2 == N, "no plan for this length");
+    static constexpr int NS = R1 == 1 ? 1 : R2 == 1 ? 2 : 3;  // stages
+    static constexpr int E = R0, TT = N / R0;                 // values per thread, threads per line
+};
+
+// Element e of a line sits at pos(e) of its LDS row.  PAD false (the lanes of a
+// wave belong to different lines, as in the column sweeps): pos(e) = e, and the
+// odd line stride LS keeps the lanes on different banks.  PAD true (neighbouring
+// lanes work on one line): one pad after every R[0] values, pos(e) = e + e / R[0],
+// so that the first stage's writes have the odd stride R[0] + 1.  Every stride
+// between a thread's own values (N / R of a stage, the butterflies' R[0]) is a
+// multiple of R[0], so a butterfly's positions are one base and immediate
+// offsets either way.  X[0] is also kept at pos(N), so that the partner X[N - k]
+// of the outputs of one butterfly sits at one base minus those offsets too.
+template <typename T, int N, bool PAD>
+struct LineFft {
+    using Pl = FftPlan<N>;
+    static constexpr int R0 = Pl::R0, E = Pl::E, TT = Pl::TT;
+    static constexpr int RL = Pl::NS == 1 ? Pl::R0 : Pl::NS == 2 ? Pl::R1 : Pl::R2;  // radix of the last stage
+    static constexpr int NBL = N / RL;                                               // its butterflies
+    static constexpr int BL = (NBL + TT - 1) / TT;                                   // and how many a thread has
+    static __device__ __forceinline__ constexpr int pos(int e) { return PAD ? e + (int)((unsigned)e / (unsigned)R0) : e; }
+    static constexpr int step(int d) { return PAD ? d + d / R0 : d; }  // of pos, for a multiple of R0
+    static constexpr int LS = (step(N) + 1) | 1;
+    static constexpr int STL = Pl::NS == 1 ? 1 : step(NBL);  // of pos between a last butterfly's outputs
+    struct Out {
+        cpx<T> v[BL][RL];
+    };
+
+    // stage of radix R after NSP points' worth of stages: butterfly j
+    template <int R, int NSP>
+    static __device__ __forceinline__ void butterfly(cpx<T> (&v)[R], const cpx<T>* ln, int j, const cpx<T>* tw) {
+        constexpr int NB = N / R;
+        const cpx<T>* p = ln + pos(j);
+#pragma unroll
+        for (int r = 0; r < R; ++r) v[r] = p[r * step(NB)];
+        const unsigned jm = (unsigned)j % (unsigned)NSP;
+#pragma unroll
+        for (int r = 1; r < R; ++r) v[r] = cmul(v[r], tw[jm * (unsigned)(r * (N / (NSP * R)))]);
+        dft<T, R>(v);
+    }
+
+    // All threads of the block call it with their line's LDS row; `ln` must be
+    // free to be written and `tw` ready.  Ends on reads of `ln`.
+    static __device__ __forceinline__ void forward(cpx<T> (&v)[E], cpx<T>* ln, int t, const cpx<T>* tw, Out& out) {
+        dft<T, E>(v);
+        if constexpr (Pl::NS == 1) {
+#pragma unroll
+            for (int r = 0; r < E; ++r) out.v[0][r] = v[r];
+        } else {
+            cpx<T>* w0 = ln + t * step(R0);
+#pragma unroll
+            for (int r = 0; r < E; ++r) w0[r] = v[r];
+            __syncthreads();
+            if constexpr (Pl::NS == 3) {
+                constexpr int R = Pl::R1, NB = N / R, B = (NB + TT - 1) / TT;
+                cpx<T> w[B][R];
+#pragma unroll
+                for (int u = 0; u < B; ++u) {
+                    const int j = t + u * TT;
+                    if (NB % TT == 0 || j < NB) butterfly<R, R0>(w[u], ln, j, tw);
+                }
+                __syncthreads();
+#pragma unroll
+                for (int u = 0; u < B; ++u) {
+                    const unsigned j = (unsigned)(t + u * TT);
+                    if (NB % TT == 0 || j < (unsigned)NB) {
+                        // element (j / R0) R0 R + j mod R0 + r R0
+                        cpx<T>* p = ln + (j / (unsigned)R0) * (unsigned)(step(R0) * R) + j % (unsigned)R0;
+#pragma unroll
+                        for (int r = 0; r < R; ++r) p[r * step(R0)] = w[u][r];
+                    }
+                }
+                __syncthreads();
+            }
+#pragma unroll
+            for (int u = 0; u < BL; ++u) {
+                const int j = t + u * TT;
+                if (NBL % TT == 0 || j < NBL) butterfly<RL, N / RL>(out.v[u], ln, j, tw);
+            }
+        }
+    }
+
+    // the outputs to the line's LDS row, X[k] at pos(k) and X[0] at pos(N) too
+    // (after every thread has ended `forward`)
+    static __device__ __forceinline__ void put(const Out& out, cpx<T>* ln, int t) {
+#pragma unroll
+        for (int u = 0; u < BL; ++u) {
+            const int j = t + u * TT;
+            if (NBL % TT == 0 || j < NBL) {
+                cpx<T>* p = ln + pos(j);
+#pragma unroll
+                for (int r = 0; r < RL; ++r) p[r * STL] = out.v[u][r];
+                if (u == 0 && t == 0) ln[pos(N)] = out.v[0][0];
+            }
+        }
+    }
+
+    // f(j, dk, X[j + dk]) for the outputs this thread holds, dk the same for
+    // every thread
+    template <class F>
+    static __device__ __forceinline__ void each(const Out& out, int t, F&& f) {
+#pragma unroll
+        for (int u = 0; u < BL; ++u) {
+            const int j = t + u * TT;
+            if (NBL % TT == 0 || j < NBL) {
+#pragma unroll
+                for (int r = 0; r < RL; ++r) f(j, r * NBL, out.v[u][r]);
+            }
+        }
+    }
+
+    // f(j, dk, X[j + dk], X[N - j - dk]): with the partner, from the LDS row that
+    // every thread has `put` its outputs to
+    template <class F>
+    static __device__ __forceinline__ void each_pair(const Out& out, const cpx<T>* ln, int t, F&& f) {
+#pragma unroll
+        for (int u = 0; u < BL; ++u) {
+            const int j = t + u * TT;
+            if (NBL % TT == 0 || j < NBL) {
+                // N - j = (RL - 1) NBL + (NBL - j): the last butterfly input's base
+                const cpx<T>* p = ln + (Pl::NS == 1 ? 1 : pos(NBL - j));
+#pragma unroll
+                for (int r = 0; r < RL; ++r) {
+                    const int back = RL - 1 - r;
+                    const cpx<T> m = Pl::NS == 1 ? ln[pos(N - r)] : p[back * STL];
+                    f(j, r * NBL, out.v[u][r], m);
+                }
+            }
+        }
+    }
+};
 
 // Forward DFT of the block's lines for N = 256 = 16 x 16 with the line held in
 // registers: the thread with column index c (0..15) of a line enters with

@@ -32,8 +32,9 @@ import statistics
 import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-KERNEL_SOURCES = ("poisson_sweeps.hip", "poisson_device.hpp", "poisson_fft.hpp", "poisson_internal.hpp",
-                  "poisson_kernels.hip", "poisson_control.hpp")
+KERNEL_SOURCES = ("poisson_sweeps.hip", "poisson_resid.hpp", "poisson_outer.hip", "poisson_columns.hpp",
+                  "poisson_update.hip", "poisson_launch.hpp", "poisson_device.hpp", "poisson_fft.hpp",
+                  "poisson_internal.hpp", "poisson_kernels.hip", "poisson_control.hpp")
 
 
 def kernel_source_hash() -> str:
