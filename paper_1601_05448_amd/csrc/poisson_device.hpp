@@ -326,9 +326,9 @@ struct ZMarch {
         rm = (ja == 0 ? ny - 1 : ja - 1) * nx;
         rp = (jb + 1 == ny ? 0 : jb + 1) * nx;
     }
-    __device__ unsigned plane(int k) const {  // periodic plane index (k >= -1)
-        return (unsigned)(k + (int)nz) % nz;
-    }
+    // periodic plane index, -1 <= k <= nz; planes past nz are loaded but not used
+    // (the steps past the last plane): plane 0
+    __device__ unsigned plane(int k) const { return k < 0 ? nz - 1 : k < (int)nz ? (unsigned)k : 0u; }
     __device__ __amdgpu_buffer_rsrc_t rsrc(const T* f, unsigned kp) const {
         return plane_rsrc(f, (unsigned long long)kp * sz * sizeof(T), sz * (unsigned)sizeof(T));
     }
@@ -352,42 +352,48 @@ struct ZMarch {
         s.ba = buffer_load<T>(bb, (ra + i) * S);
         s.bb = buffer_load<T>(bb, (rb + i) * S);
     }
-    // The columns beyond a wave's edges come from the neighbouring waves through
-    // LDS: `edge` holds, per strip, two slots (lane 0, lane 63) of 4 values for
-    // each group of 64 columns.  put: edge lanes publish their values; get (after
-    // a barrier): lane 0 reads the left neighbour group's lane 63, lane 63 the
-    // right neighbour group's lane 0 (periodic in x).
-    __device__ void edge_put(T* edge, unsigned col, const PlaneRows<T>& c) const {
-        if (lane == 0 || lane == 63) {
-            T* e = edge + ((col / 64) * 2 + (lane == 63 ? 1 : 0)) * 4;
-            e[0] = c.pa;
-            e[1] = c.pb;
-            e[2] = c.ra;
-            e[3] = c.rb;
+    // The x neighbours' values.  DPP (rows of whole waves): from the neighbouring
+    // lanes by DPP, and beyond a wave's edges from the neighbouring waves through
+    // `xb`, which holds, per strip, two slots (lane 0, lane 63) for each group of 64
+    // columns.  Otherwise `xb` holds every column of the strip.  put: publish the
+    // thread's values; get (after a barrier): those of columns col - 1 and col + 1
+    // (periodic in x).
+    template <bool DPP>
+    __device__ void x_put(PlaneRows<T>* xb, unsigned col, const PlaneRows<T>& c) const {
+        if constexpr (DPP) {
+            if (lane == 0 || lane == 63) xb[(col / 64) * 2 + (lane == 63 ? 1 : 0)] = c;
+        } else {
+            xb[col] = c;
         }
     }
-    __device__ PlaneRows<T> edge_get(const T* edge, unsigned col) const {
-        const unsigned grp = nx / 64, g = col / 64;
-        const unsigned slot = (lane == 0) ? ((g + grp - 1) % grp) * 2 + 1 : ((g + 1) % grp) * 2;
-        const T* e = edge + slot * 4;
-        return PlaneRows<T>{e[0], e[1], e[2], e[3]};
+    template <bool DPP>
+    __device__ void x_get(const PlaneRows<T>* xb, unsigned col, const PlaneRows<T>& c, PlaneRows<T>& xm,
+                          PlaneRows<T>& xp) const {
+        if constexpr (DPP) {
+            const unsigned grp = nx / 64, g = col / 64;
+            const unsigned slot = (lane == 0) ? (g == 0 ? grp - 1 : g - 1) * 2 + 1 : (g + 1 == grp ? 0 : g + 1) * 2;
+            const PlaneRows<T> ex = xb[slot];
+            xm.pa = dpp_move<kDppWaveShr1>(c.pa, ex.pa);
+            xp.pa = dpp_move<kDppWaveShl1>(c.pa, ex.pa);
+            xm.pb = dpp_move<kDppWaveShr1>(c.pb, ex.pb);
+            xp.pb = dpp_move<kDppWaveShl1>(c.pb, ex.pb);
+            xm.ra = dpp_move<kDppWaveShr1>(c.ra, ex.ra);
+            xp.ra = dpp_move<kDppWaveShl1>(c.ra, ex.ra);
+            xm.rb = dpp_move<kDppWaveShr1>(c.rb, ex.rb);
+            xp.rb = dpp_move<kDppWaveShl1>(c.rb, ex.rb);
+        } else {
+            xm = xb[col == 0 ? nx - 1 : col - 1];
+            xp = xb[col + 1 == nx ? 0 : col + 1];
+        }
     }
     // the 26 stencil inputs of the pair at plane k from planes k-1 (zm), k (c), k+1
-    // (zp); x neighbours by DPP, the edge lanes taking `ex` (from edge_get)
+    // (zp) and the x neighbours at plane k
     __device__ void pair(const PlaneRows<T>& zm, const PlaneRows<T>& c, const PlaneRows<T>& zp,
-                         const PlaneSide<T>& s, const PlaneRows<T>& ex, PairIn<T>& in) const {
-        const T pa_xm = dpp_move<kDppWaveShr1>(c.pa, ex.pa);
-        const T pa_xp = dpp_move<kDppWaveShl1>(c.pa, ex.pa);
-        const T pb_xm = dpp_move<kDppWaveShr1>(c.pb, ex.pb);
-        const T pb_xp = dpp_move<kDppWaveShl1>(c.pb, ex.pb);
-        const T ra_xm = dpp_move<kDppWaveShr1>(c.ra, ex.ra);
-        const T ra_xp = dpp_move<kDppWaveShl1>(c.ra, ex.ra);
-        const T rb_xm = dpp_move<kDppWaveShr1>(c.rb, ex.rb);
-        const T rb_xp = dpp_move<kDppWaveShl1>(c.rb, ex.rb);
+                         const PlaneSide<T>& s, const PlaneRows<T>& xm, const PlaneRows<T>& xp, PairIn<T>& in) const {
         // order of PairIn: a, b, a x-, a x+, b x-, b x+, a y-, b y+, a z-, a z+, b z-, b z+
-        in.r[0] = c.ra;  in.r[1] = c.rb;  in.r[2] = ra_xm; in.r[3] = ra_xp; in.r[4] = rb_xm; in.r[5] = rb_xp;
+        in.r[0] = c.ra;  in.r[1] = c.rb;  in.r[2] = xm.ra; in.r[3] = xp.ra; in.r[4] = xm.rb; in.r[5] = xp.rb;
         in.r[6] = s.rym; in.r[7] = s.ryp; in.r[8] = zm.ra; in.r[9] = zp.ra; in.r[10] = zm.rb; in.r[11] = zp.rb;
-        in.q[0] = c.pa;  in.q[1] = c.pb;  in.q[2] = pa_xm; in.q[3] = pa_xp; in.q[4] = pb_xm; in.q[5] = pb_xp;
+        in.q[0] = c.pa;  in.q[1] = c.pb;  in.q[2] = xm.pa; in.q[3] = xp.pa; in.q[4] = xm.pb; in.q[5] = xp.pb;
         in.q[6] = s.pym; in.q[7] = s.pyp; in.q[8] = zm.pa; in.q[9] = zp.pa; in.q[10] = zm.pb; in.q[11] = zp.pb;
         in.ba = s.ba;
         in.bb = s.bb;
@@ -404,36 +410,6 @@ __device__ __forceinline__ unsigned xcd_block(unsigned b, unsigned nb) {
     constexpr unsigned kXcds = 8;
     return (nb % kXcds != 0) ? b : (b % kXcds) * (nb / kXcds) + b / kXcds;
 }
-
-// Thread layout of a z-marching tile for rows of length N handled by NT
-// threads: SUB strips (row pairs) of N threads each when N < NT, or CPT columns
-// per thread when N >= NT.  A tile marches KM planes; every KF planes its L = SUB
-// KF lines are full and are transformed and written out ("flushed"), so that the
-// two z halo planes a tile reads are shared by KM >= KMIN planes however few
-// lines the transform's LDS holds.
-template <int N, int NT, int L, int KMIN = 16>
-struct ZTile {
-    static constexpr int CPT = N >= NT ? N / NT : 1;
-    static constexpr int SUB = N >= NT ? 1 : NT / N;
-    static constexpr int KF = L / SUB;
-    static constexpr int KM = KF >= KMIN ? KF : KMIN;
-    static constexpr int EDGE = (N / 64) * 2 * 4;  // edge values per strip and buffer
-    static_assert(N % 64 == 0, "columns must fill whole waves");
-    static_assert(SUB * KF == L && (N >= NT ? N % NT == 0 : NT % N == 0), "tile shape");
-    static_assert(KM % KF == 0 && KF % 2 == 0, "flushes");
-};
-
-// Tiles of the residual sweep P1 and of the fused FP32 outer residual: 32
-// planes (halo planes shared by twice as many) for FP64 and for FP32 rows of
-// 1024 cells; the FP32 sweep on shorter rows keeps 16, which keeps it within
-// 128 registers (four waves per SIMD) and, at 512 cells, with two blocks per
-// CU, lets neighbouring tiles stay closer in z, so that more of the y halo rows
-// they read from each other are still in L2 (measured at 512^3: 1.19 instead
-// of 1.38 of the algorithmic bytes, 7% faster).
-template <typename T, int N>
-using P1Tile = ZTile<N, LineCfg<T, N>::NT, LineCfg<T, N>::L, (sizeof(T) == 8 || N >= 1024) ? 32 : 16>;
-template <int N>
-using OuterTile = ZTile<N, LineCfg<float, N>::NT, LineCfg<float, N>::L, 32>;
 
 // One cell, plain IEEE divisions: the stand-alone operator and residual sweeps
 // (parity checks), which need no state and are off the iteration's path.

@@ -315,31 +315,41 @@ __device__ __forceinline__ void fft_block_lines(cpx<T>* lds, const cpx<T>* tw) {
 // and leaves with the outputs of its butterflies of the last stage, X[k] at
 // k = t + u TT + r N/R.  A two-stage line passes LDS once (three stages: twice)
 // where stages that start and end in LDS pass it N_stages + 1 times.
-constexpr int plan_radix(int n, int s) {
+// Three sets: 0 with the fewest stages (the column sweeps); 1 with eight values per
+// thread (the sweeps along x, whose threads hold a stencil's planes or an update's
+// values besides, and whose N / 8 threads per line fit their tiles); 2 the same
+// but sixteen values at 256 and 512 (the FP64 stencil sweeps, which run one or two
+// large blocks per CU and gain more from fewer barriers than from fewer registers).
+constexpr int plan_radix(int set, int n, int s) {
     int r[3] = {0, 1, 1};
+    auto plan = [&](int a, int b, int c) {
+        r[0] = a;
+        r[1] = b;
+        r[2] = c;
+    };
     switch (n) {
-        case 4: case 6: case 8: case 12: r[0] = n; break;
-        case 16: r[0] = 4; r[1] = 4; break;
-        case 24: r[0] = 6; r[1] = 4; break;
-        case 32: r[0] = 8; r[1] = 4; break;
-        case 48: r[0] = 12; r[1] = 4; break;
-        case 64: r[0] = 8; r[1] = 8; break;
-        case 96: r[0] = 12; r[1] = 8; break;
-        case 128: r[0] = 16; r[1] = 8; break;
-        case 192: r[0] = 12; r[1] = 16; break;
-        case 256: r[0] = 16; r[1] = 16; break;
-        case 384: r[0] = 12; r[1] = 8; r[2] = 4; break;
-        case 512: r[0] = 8; r[1] = 8; r[2] = 8; break;
-        case 768: r[0] = 12; r[1] = 8; r[2] = 8; break;
-        case 1024: r[0] = 16; r[1] = 8; r[2] = 8; break;
+        case 4: case 6: case 8: case 12: plan(n, 1, 1); break;
+        case 16: set == 0 ? plan(4, 4, 1) : plan(8, 2, 1); break;
+        case 24: set == 0 ? plan(6, 4, 1) : plan(8, 3, 1); break;
+        case 32: plan(8, 4, 1); break;
+        case 48: set == 0 ? plan(12, 4, 1) : plan(8, 6, 1); break;
+        case 64: plan(8, 8, 1); break;
+        case 96: set == 0 ? plan(12, 8, 1) : plan(8, 4, 3); break;
+        case 128: set == 0 ? plan(16, 8, 1) : plan(8, 4, 4); break;
+        case 192: set == 0 ? plan(12, 16, 1) : plan(8, 8, 3); break;
+        case 256: set == 1 ? plan(8, 8, 4) : plan(16, 16, 1); break;
+        case 384: set == 0 ? plan(12, 8, 4) : plan(8, 8, 6); break;
+        case 512: set == 2 ? plan(16, 8, 4) : plan(8, 8, 8); break;
+        case 768: set == 0 ? plan(12, 8, 8) : plan(8, 8, 12); break;
+        case 1024: plan(16, 8, 8); break;
         default: break;
     }
     return r[s];
 }
 
-template <int N>
+template <int N, int SET = 0>
 struct FftPlan {
-    static constexpr int R0 = plan_radix(N, 0), R1 = plan_radix(N, 1), R2 = plan_radix(N, 2);
+    static constexpr int R0 = plan_radix(SET, N, 0), R1 = plan_radix(SET, N, 1), R2 = plan_radix(SET, N, 2);
     static_assert(R0 * R1 * R2 == N, "no plan for this length");
     static constexpr int NS = R1 == 1 ? 1 : R2 == 1 ? 2 : 3;  // stages
     static constexpr int E = R0, TT = N / R0;                 // values per thread, threads per line
@@ -348,26 +358,39 @@ struct FftPlan {
 // Element e of a line sits at pos(e) of its LDS row.  PAD false (the lanes of a
 // wave belong to different lines, as in the column sweeps): pos(e) = e, and the
 // odd line stride LS keeps the lanes on different banks.  PAD true (neighbouring
-// lanes work on one line): one pad after every R[0] values, pos(e) = e + e / R[0],
-// so that the first stage's writes have the odd stride R[0] + 1.  Every stride
+// lanes work on one line): one pad after every PU values, pos(e) = e + e / PU, so
+// that the first stage's writes, R[0] apart, spread over the banks.  PU = R[0], or
+// 16 where R[0] = 8 and every stage's N / R is a multiple of 16.  Every stride
 // between a thread's own values (N / R of a stage, the butterflies' R[0]) is a
-// multiple of R[0], so a butterfly's positions are one base and immediate
-// offsets either way.  X[0] is also kept at pos(N), so that the partner X[N - k]
+// multiple of PU (or of 8, from a base below 8 mod 16), so a butterfly's positions
+// are one base and immediate offsets either way.  X[0] is also kept at pos(N), so that the partner X[N - k]
 // of the outputs of one butterfly sits at one base minus those offsets too.
-template <typename T, int N, bool PAD>
+template <typename T, int N, bool PAD, int SET = 0>
 struct LineFft {
-    using Pl = FftPlan<N>;
+    using Pl = FftPlan<N, SET>;
     static constexpr int R0 = Pl::R0, E = Pl::E, TT = Pl::TT;
+    static constexpr int PU =
+        R0 == 8 && Pl::NS == 3 && (N / Pl::R1) % 16 == 0 && (N / Pl::R2) % 16 == 0 ? 16 : R0;
     static constexpr int RL = Pl::NS == 1 ? Pl::R0 : Pl::NS == 2 ? Pl::R1 : Pl::R2;  // radix of the last stage
     static constexpr int NBL = N / RL;                                               // its butterflies
     static constexpr int BL = (NBL + TT - 1) / TT;                                   // and how many a thread has
-    static __device__ __forceinline__ constexpr int pos(int e) { return PAD ? e + (int)((unsigned)e / (unsigned)R0) : e; }
-    static constexpr int step(int d) { return PAD ? d + d / R0 : d; }  // of pos, for a multiple of R0
+    static __device__ __forceinline__ constexpr int pos(int e) { return PAD ? e + (int)((unsigned)e / (unsigned)PU) : e; }
+    static constexpr int step(int d) { return PAD ? d + d / PU : d; }  // of pos, for a multiple of R0
     static constexpr int LS = (step(N) + 1) | 1;
-    static constexpr int STL = Pl::NS == 1 ? 1 : step(NBL);  // of pos between a last butterfly's outputs
     struct Out {
         cpx<T> v[BL][RL];
     };
+
+    // The thread index for a stage whose butterflies do not divide evenly (OK: they
+    // do).  Under the guard j = t + u TT < NB the compiler may turn that sum into an
+    // or; merged with an equal sum outside the guard it gives wrong positions there
+    // (seen with TT = 24: t + 48 read as t | 48 for t >= 16), so the guarded sums
+    // start from a value of their own.
+    template <bool OK>
+    static __device__ __forceinline__ int own_index(int t) {
+        if constexpr (!OK) asm volatile("" : "+v"(t));
+        return t;
+    }
 
     // stage of radix R after NSP points' worth of stages: butterfly j
     template <int R, int NSP>
@@ -375,7 +398,7 @@ struct LineFft {
         constexpr int NB = N / R;
         const cpx<T>* p = ln + pos(j);
 #pragma unroll
-        for (int r = 0; r < R; ++r) v[r] = p[r * step(NB)];
+        for (int r = 0; r < R; ++r) v[r] = p[step(r * NB)];
         const unsigned jm = (unsigned)j % (unsigned)NSP;
 #pragma unroll
         for (int r = 1; r < R; ++r) v[r] = cmul(v[r], tw[jm * (unsigned)(r * (N / (NSP * R)))]);
@@ -383,42 +406,48 @@ struct LineFft {
     }
 
     // All threads of the block call it with their line's LDS row; `ln` must be
-    // free to be written and `tw` ready.  Ends on reads of `ln`.
-    static __device__ __forceinline__ void forward(cpx<T> (&v)[E], cpx<T>* ln, int t, const cpx<T>* tw, Out& out) {
+    // free to be written and `tw` ready.  Ends on reads of `ln`.  Threads without
+    // a line pass on = false and only take part in the barriers.
+    static __device__ __forceinline__ void forward(cpx<T> (&v)[E], cpx<T>* ln, int t, const cpx<T>* tw, Out& out,
+                                                   bool on = true) {
         dft<T, E>(v);
         if constexpr (Pl::NS == 1) {
 #pragma unroll
             for (int r = 0; r < E; ++r) out.v[0][r] = v[r];
         } else {
-            cpx<T>* w0 = ln + t * step(R0);
+            if (on) {
+                cpx<T>* w0 = ln + pos(t * R0);
 #pragma unroll
-            for (int r = 0; r < E; ++r) w0[r] = v[r];
+                for (int r = 0; r < E; ++r) w0[r] = v[r];
+            }
             __syncthreads();
             if constexpr (Pl::NS == 3) {
                 constexpr int R = Pl::R1, NB = N / R, B = (NB + TT - 1) / TT;
                 cpx<T> w[B][R];
+                const int tm = own_index<NB % TT == 0>(t);
 #pragma unroll
                 for (int u = 0; u < B; ++u) {
-                    const int j = t + u * TT;
-                    if (NB % TT == 0 || j < NB) butterfly<R, R0>(w[u], ln, j, tw);
+                    const int j = tm + u * TT;
+                    if (on && (NB % TT == 0 || j < NB)) butterfly<R, R0>(w[u], ln, j, tw);
                 }
                 __syncthreads();
 #pragma unroll
                 for (int u = 0; u < B; ++u) {
-                    const unsigned j = (unsigned)(t + u * TT);
-                    if (NB % TT == 0 || j < (unsigned)NB) {
+                    const unsigned j = (unsigned)(tm + u * TT);
+                    if (on && (NB % TT == 0 || j < (unsigned)NB)) {
                         // element (j / R0) R0 R + j mod R0 + r R0
-                        cpx<T>* p = ln + (j / (unsigned)R0) * (unsigned)(step(R0) * R) + j % (unsigned)R0;
+                        cpx<T>* p = ln + (j / (unsigned)R0) * (unsigned)step(R0 * R) + j % (unsigned)R0;
 #pragma unroll
-                        for (int r = 0; r < R; ++r) p[r * step(R0)] = w[u][r];
+                        for (int r = 0; r < R; ++r) p[step(r * R0)] = w[u][r];
                     }
                 }
                 __syncthreads();
             }
+            const int tl = own_index<NBL % TT == 0>(t);
 #pragma unroll
             for (int u = 0; u < BL; ++u) {
-                const int j = t + u * TT;
-                if (NBL % TT == 0 || j < NBL) butterfly<RL, N / RL>(out.v[u], ln, j, tw);
+                const int j = tl + u * TT;
+                if (on && (NBL % TT == 0 || j < NBL)) butterfly<RL, N / RL>(out.v[u], ln, j, tw);
             }
         }
     }
@@ -426,13 +455,14 @@ struct LineFft {
     // the outputs to the line's LDS row, X[k] at pos(k) and X[0] at pos(N) too
     // (after every thread has ended `forward`)
     static __device__ __forceinline__ void put(const Out& out, cpx<T>* ln, int t) {
+        t = own_index<NBL % TT == 0>(t);
 #pragma unroll
         for (int u = 0; u < BL; ++u) {
             const int j = t + u * TT;
             if (NBL % TT == 0 || j < NBL) {
                 cpx<T>* p = ln + pos(j);
 #pragma unroll
-                for (int r = 0; r < RL; ++r) p[r * STL] = out.v[u][r];
+                for (int r = 0; r < RL; ++r) p[Pl::NS == 1 ? pos(r) : step(r * NBL)] = out.v[u][r];
                 if (u == 0 && t == 0) ln[pos(N)] = out.v[0][0];
             }
         }
@@ -442,6 +472,7 @@ struct LineFft {
     // every thread
     template <class F>
     static __device__ __forceinline__ void each(const Out& out, int t, F&& f) {
+        t = own_index<NBL % TT == 0>(t);
 #pragma unroll
         for (int u = 0; u < BL; ++u) {
             const int j = t + u * TT;
@@ -456,6 +487,7 @@ struct LineFft {
     // every thread has `put` its outputs to
     template <class F>
     static __device__ __forceinline__ void each_pair(const Out& out, const cpx<T>* ln, int t, F&& f) {
+        t = own_index<NBL % TT == 0>(t);
 #pragma unroll
         for (int u = 0; u < BL; ++u) {
             const int j = t + u * TT;
@@ -465,7 +497,7 @@ struct LineFft {
 #pragma unroll
                 for (int r = 0; r < RL; ++r) {
                     const int back = RL - 1 - r;
-                    const cpx<T> m = Pl::NS == 1 ? ln[pos(N - r)] : p[back * STL];
+                    const cpx<T> m = Pl::NS == 1 ? ln[pos(N - r)] : p[step(back * NBL)];
                     f(j, r * NBL, out.v[u][r], m);
                 }
             }

@@ -6,6 +6,7 @@
 
 #include "poisson_device.hpp"
 #include "poisson_launch.hpp"
+#include "poisson_rows.hpp"
 
 namespace pois {
 
@@ -16,41 +17,41 @@ namespace pois {
 // gives r32 (stored for the later inner sweeps) and q, whose lines are
 // transformed along x into W32 exactly as the FP32 P1 would.  The mean of r32,
 // which the FP32 P1 removes, is FP64 rounding noise here and is not removed.
-// Per tile: r^2, bt^2, p, p^2, r in FP64.  One column per thread.  write = 0:
-// the sums alone (the final check of a solve, which usually ends it: no r32,
-// no transform, no W32).
+// Per tile: r^2, bt^2, p, p^2, r in FP64.  write = 0: the sums alone (the final
+// check of a solve, which usually ends it: no r32, no transform, no W32).
 template <int N, int COEF, int WEIGHT, int BCX>
-__global__ void __launch_bounds__((LineCfg<float, N>::NT), (LineCfg<float, N>::MINB))
-k_outer_resid_dhtx(GridArgs g, const Slot* __restrict__ slots, Tables tb, int write) {
-    using C = LineCfg<float, N>;
-    using Z = OuterTile<N>;
-    static_assert(Z::CPT == 1, "one marching column per thread");
-    __shared__ cpx<float> lds[C::L * C::LS];
+__global__ void __launch_bounds__((RowTile<N, true>::NT), 2)
+k_outer_resid_dhtx(GridArgs g, const Slot* __restrict__ slots, Tables tb, int write, int nflush) {
+    using Z = RowTile<N, true>;
+    using RF = RowFlush<double, N>;
+    using LF = LineFft<float, N, true, RF::SET>;
+    constexpr int KF = RF::KF;
+    __shared__ cpx<float> lds[Z::SUB * KF * LF::LS];
     __shared__ cpx<float> tw[N];
-    __shared__ double red[(C::NT / 64) * 5];
-    __shared__ double edge[2 * Z::SUB * Z::EDGE];
+    __shared__ double red[(Z::NT / 64) * 5];
+    __shared__ PlaneRows<double> xb[2 * Z::SUB * Z::XV];
     const Slot& s = slots[blockIdx.y];
     SolveState* st = s.st;
     if (st->done || st->stage != 0) return;
     const cpx<float>* twg = twiddles<float>(tb, 0);
     const cpx<float>* twc = dct_twiddles<float>(tb);
-    for (int e = threadIdx.x; e < N; e += C::NT) tw[e] = twg[e];
+    for (int e = threadIdx.x; e < N; e += Z::NT) tw[e] = twg[e];
     const double bm = st->b_mean, inv_s = st->inv_s, rmax = st->rho_max, rinv = recip(st->rho_max);
 
-    const unsigned nyh = (unsigned)g.ny / 2, nz = (unsigned)g.nz;
-    const unsigned ngj = (nyh + Z::SUB - 1) / Z::SUB, ngk = (nz + Z::KM - 1) / Z::KM;
+    const unsigned nyh = (unsigned)g.ny / 2, nz = (unsigned)g.nz, km = (unsigned)(nflush * KF);
+    const unsigned ngj = (nyh + Z::SUB - 1) / Z::SUB, ngk = (nz + km - 1) / km;
     const unsigned ntiles = ngj * ngk;
-    const int sidx = (N >= C::NT) ? 0 : (int)threadIdx.x / N;
-    const unsigned i = (N >= C::NT) ? threadIdx.x : threadIdx.x % N;
+    const int sidx = (int)threadIdx.x / Z::MT;
+    const unsigned col0 = threadIdx.x % Z::MT;
     POIS_GLOBAL float* r32 = gptr(s.r32);
     POIS_GLOBAL float* W32 = gptr(s.W32);
     ZMarch<double> zm;
     zm.p = s.p;
     zm.rho = s.rho;
     zm.rhs = s.b;
-    zm.nx = (unsigned)g.nx;
+    zm.nx = (unsigned)N;
     zm.nz = nz;
-    zm.sz = (unsigned)g.nx * (unsigned)g.ny;
+    zm.sz = (unsigned)N * (unsigned)g.ny;
     zm.lane = (int)(threadIdx.x & 63);
     double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
 
@@ -59,111 +60,226 @@ k_outer_resid_dhtx(GridArgs g, const Slot* __restrict__ slots, Tables tb, int wr
         const unsigned jp = tj * Z::SUB + sidx;
         const bool jvalid = jp < nyh;
         zm.rows_of(jvalid ? jp : 0u, (unsigned)g.ny);
-        const int k0 = (int)(tk * Z::KM);
-        PlaneRows<double> pl[3];
-        PlaneSide<double> sd;
-        zm.load_rows(zm.plane(k0 - 1), i, pl[0]);
-        zm.load_rows(zm.plane(k0), i, pl[1]);
-        zm.load_rows(zm.plane(k0 + 1), i, pl[2]);
-        zm.load_side(zm.plane(k0), i, sd);
-        double zc[2];  // the lower z faces of the pair, carried from plane to plane (COEF 0)
-        for (int f = 0; f < Z::KM / Z::KF; ++f) {
+        const int k0 = (int)(tk * km);
+        PlaneRows<double> pl[Z::CPT][3];
+        PlaneSide<double> sd[Z::CPT];
 #pragma unroll
-            for (int q = 0; q < Z::KF; ++q) {
-                const int k = k0 + f * Z::KF + q;
+        for (int c = 0; c < Z::CPT; ++c) {
+            const unsigned i = col0 + c * Z::MT;
+            zm.load_rows(zm.plane(k0 - 1), i, pl[c][0]);
+            zm.load_rows(zm.plane(k0), i, pl[c][1]);
+            zm.load_rows(zm.plane(k0 + 1), i, pl[c][2]);
+            zm.load_side(zm.plane(k0), i, sd[c]);
+        }
+        // the lower z faces of the pair, carried from plane to plane (COEF 0)
+        constexpr bool kZC = COEF == 0 && Z::CPT == 1;
+        double zc[Z::CPT][2];
+        for (int f = 0; f < nflush && k0 + f * KF < (int)nz; ++f) {
+#pragma unroll
+            for (int q = 0; q < KF; ++q) {
+                const int k = k0 + f * KF + q;
                 const bool valid = jvalid && k < (int)nz;
-                PlaneRows<double> nn;
-                PlaneSide<double> ns;
+                PlaneRows<double> nn[Z::CPT];
+                PlaneSide<double> ns[Z::CPT];
                 __builtin_amdgcn_s_setprio(2);
-                zm.load_rows(zm.plane(k + 2), i, nn);
-                zm.load_side(zm.plane(k + 1), i, ns);
-                __builtin_amdgcn_s_setprio(0);
-                double* eb = edge + ((q & 1) * Z::SUB + sidx) * Z::EDGE;
-                zm.edge_put(eb, i, pl[1]);
-                __syncthreads();
-                PairIn<double> in;
-                zm.pair(pl[0], pl[1], pl[2], sd, zm.edge_get(eb, i), in);
-                cpx<float> qv = {0.0f, 0.0f};
-                if (valid) {
-                    if constexpr (COEF == 0)
-                        if (q == 0 && f == 0) z_faces_below(in, rinv, zc);
-                    const PairOut<double> pr =
-                        pair_eval<double, COEF, WEIGHT, COEF == 0>(g, in, bm, rmax, rinv, BCX ? x_walls(g, i) : 0u, zc);
-                    acc[0] += pr.a.r * pr.a.r + pr.b.r * pr.b.r;
-                    acc[1] += pr.a.bt * pr.a.bt + pr.b.bt * pr.b.bt;
-                    acc[2] += pr.a.pc + pr.b.pc;
-                    acc[3] += pr.a.pc * pr.a.pc + pr.b.pc * pr.b.pc;
-                    acc[4] += pr.a.r + pr.b.r;
-                    if (write) {
-                        const float ra = (float)(pr.a.r * inv_s), rb = (float)(pr.b.r * inv_s);
-                        const unsigned a = (unsigned)k * zm.sz + zm.ra + i;
-                        __builtin_nontemporal_store(ra, &r32[a]);  // streaming (see k_resid_dhtx_z)
-                        __builtin_nontemporal_store(rb, &r32[a + (unsigned)g.nx]);
-                        qv = {(float)pr.a.w * ra, (float)pr.b.w * rb};
-                    }
+#pragma unroll
+                for (int c = 0; c < Z::CPT; ++c) {
+                    const unsigned i = col0 + c * Z::MT;
+                    zm.load_rows(zm.plane(k + 2), i, nn[c]);
+                    zm.load_side(zm.plane(k + 1), i, ns[c]);
                 }
-                if (write) lds[(sidx * Z::KF + q) * C::LS + C::pos(x_slot(i, N, BCX))] = qv;
-                pl[0] = pl[1];
-                pl[1] = pl[2];
-                pl[2] = nn;
-                sd = ns;
+                __builtin_amdgcn_s_setprio(0);
+                PlaneRows<double>* eb = xb + ((q & 1) * Z::SUB + sidx) * Z::XV;
+#pragma unroll
+                for (int c = 0; c < Z::CPT; ++c) zm.template x_put<Z::DPP>(eb, col0 + c * Z::MT, pl[c][1]);
+                __syncthreads();
+#pragma unroll
+                for (int c = 0; c < Z::CPT; ++c) {
+                    const unsigned i = col0 + c * Z::MT;
+                    PairIn<double> in;
+                    PlaneRows<double> xm, xp;
+                    zm.template x_get<Z::DPP>(eb, i, pl[c][1], xm, xp);
+                    zm.pair(pl[c][0], pl[c][1], pl[c][2], sd[c], xm, xp, in);
+                    cpx<float> qv = {0.0f, 0.0f};
+                    if (valid) {
+                        if constexpr (kZC)
+                            if (q == 0 && f == 0) z_faces_below(in, rinv, zc[c]);
+                        const PairOut<double> pr =
+                            pair_eval<double, COEF, WEIGHT, kZC>(g, in, bm, rmax, rinv, BCX ? x_walls(g, i) : 0u, zc[c]);
+                        acc[0] += pr.a.r * pr.a.r + pr.b.r * pr.b.r;
+                        acc[1] += pr.a.bt * pr.a.bt + pr.b.bt * pr.b.bt;
+                        acc[2] += pr.a.pc + pr.b.pc;
+                        acc[3] += pr.a.pc * pr.a.pc + pr.b.pc * pr.b.pc;
+                        acc[4] += pr.a.r + pr.b.r;
+                        if (write) {
+                            const float ra = (float)(pr.a.r * inv_s), rb = (float)(pr.b.r * inv_s);
+                            const unsigned at = (unsigned)k * zm.sz + i;
+                            __builtin_nontemporal_store(ra, &r32[at + zm.ra]);  // streaming (see k_resid_dhtx_z)
+                            __builtin_nontemporal_store(rb, &r32[at + zm.rb]);
+                            qv = {(float)pr.a.w * ra, (float)pr.b.w * rb};
+                        }
+                    }
+                    if (write) lds[(q * Z::SUB + sidx) * LF::LS + LF::pos((int)x_slot(i, N, BCX))] = qv;
+                }
+#pragma unroll
+                for (int c = 0; c < Z::CPT; ++c) {
+                    pl[c][0] = pl[c][1];
+                    pl[c][1] = pl[c][2];
+                    pl[c][2] = nn[c];
+                    sd[c] = ns[c];
+                }
             }
             if (!write) continue;  // uniform
             __syncthreads();
-            fft_block_lines<float, N>(lds, tw);
-#pragma unroll
-            for (int it = 0; it < C::IT; ++it) {
-                const int e = threadIdx.x + it * C::NT;
-                const int l = e / N, kx = e % N;
-                const unsigned ljp = tj * Z::SUB + l / Z::KF;
-                const unsigned lk = (unsigned)(k0 + f * Z::KF) + l % Z::KF;
-                if (ljp < nyh && lk < nz) {
-                    const unsigned P = lk * nyh + ljp;
-                    const cpx<float> h = x_forward_out<float, N>(lds + l * C::LS, kx, BCX, twc);
-                    __builtin_nontemporal_store(h.x, &W32[(2 * P) * N + kx]);
-                    __builtin_nontemporal_store(h.y, &W32[(2 * P + 1) * N + kx]);
+            const int kf = k0 + f * KF;
+            transform_rows<float, N, RF::SET, Z::SUB, KF, Z::CPT>(lds, tw, BCX, twc, sidx, col0,
+                                                                   [&](int q, int c, cpx<float> h) {
+                if (jvalid && kf + q < (int)nz) {
+                    const unsigned at = (unsigned)(kf + q) * zm.sz + col0 + c * Z::MT;
+                    __builtin_nontemporal_store(h.x, &W32[at + zm.ra]);
+                    __builtin_nontemporal_store(h.y, &W32[at + zm.rb]);
                 }
-            }
+            });
             __syncthreads();  // the next flush overwrites the lines
         }
-        put_unit_sums<C::NT, 5>(acc, red, s.partial + (unsigned long long)tile * kPartialStride);
+        put_unit_sums<Z::NT, 5>(acc, red, s.partial + (unsigned long long)tile * kPartialStride);
     }
 }
 
-template <int N>
-constexpr bool outer_fusable_len() {
-    if constexpr (N % 64 != 0) return false;
-    else return OuterTile<N>::CPT == 1;
+// The same on small grids, every load of a tile issued at once (see k_resid_dhtx_s).
+template <int N, int KF, int COEF, int WEIGHT>
+__global__ void __launch_bounds__((RowTile<N, false>::NT))
+k_outer_resid_dhtx_s(GridArgs g, const Slot* __restrict__ slots, Tables tb, int write) {
+    using Z = RowTile<N, false>;
+    using LF = LineFft<float, N, true, 1>;
+    static_assert(Z::CPT == 1, "one column per thread");
+    __shared__ cpx<float> lds[Z::SUB * KF * LF::LS];
+    __shared__ cpx<float> tw[N];
+    __shared__ double red[(Z::NT / 64) * 5];
+    __shared__ PlaneRows<double> xb[KF * Z::SUB * Z::XV];
+    const Slot& s = slots[blockIdx.y];
+    SolveState* st = s.st;
+    if (st->done || st->stage != 0) return;
+    const cpx<float>* twg = twiddles<float>(tb, 0);
+    const cpx<float>* twc = dct_twiddles<float>(tb);
+    for (int e = threadIdx.x; e < N; e += Z::NT) tw[e] = twg[e];
+    const double bm = st->b_mean, inv_s = st->inv_s, rmax = st->rho_max, rinv = recip(st->rho_max);
+
+    const unsigned nyh = (unsigned)g.ny / 2, nz = (unsigned)g.nz;
+    const unsigned ngj = (nyh + Z::SUB - 1) / Z::SUB, ngk = (nz + KF - 1) / KF;
+    const unsigned ntiles = ngj * ngk;
+    const int sidx = (int)threadIdx.x / N;
+    const unsigned i = threadIdx.x % N;
+    POIS_GLOBAL float* r32 = gptr(s.r32);
+    POIS_GLOBAL float* W32 = gptr(s.W32);
+    ZMarch<double> zm;
+    zm.p = s.p;
+    zm.rho = s.rho;
+    zm.rhs = s.b;
+    zm.nx = (unsigned)N;
+    zm.nz = nz;
+    zm.sz = (unsigned)N * (unsigned)g.ny;
+    zm.lane = (int)(threadIdx.x & 63);
+    double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    for (unsigned tile = xcd_block(blockIdx.x, gridDim.x); tile < ntiles; tile += gridDim.x) {
+        const unsigned tj = tile % ngj, tk = tile / ngj;
+        const unsigned jp = tj * Z::SUB + sidx;
+        const bool jvalid = jp < nyh;
+        zm.rows_of(jvalid ? jp : 0u, (unsigned)g.ny);
+        const int k0 = (int)(tk * KF);
+        PlaneRows<double> pl[KF + 2];
+        PlaneSide<double> sd[KF];
+#pragma unroll
+        for (int q = 0; q < KF + 2; ++q) zm.load_rows(zm.plane(k0 + q - 1), i, pl[q]);
+#pragma unroll
+        for (int q = 0; q < KF; ++q) zm.load_side(zm.plane(k0 + q), i, sd[q]);
+#pragma unroll
+        for (int q = 0; q < KF; ++q)
+            zm.template x_put<Z::DPP>(xb + (q * Z::SUB + sidx) * Z::XV, i, pl[q + 1]);
+        __syncthreads();
+        double zc[2];
+#pragma unroll
+        for (int q = 0; q < KF; ++q) {
+            const bool valid = jvalid && k0 + q < (int)nz;
+            PairIn<double> in;
+            PlaneRows<double> xm, xp;
+            zm.template x_get<Z::DPP>(xb + (q * Z::SUB + sidx) * Z::XV, i, pl[q + 1], xm, xp);
+            zm.pair(pl[q], pl[q + 1], pl[q + 2], sd[q], xm, xp, in);
+            cpx<float> qv = {0.0f, 0.0f};
+            if (valid) {
+                if constexpr (COEF == 0)
+                    if (q == 0) z_faces_below(in, rinv, zc);
+                const PairOut<double> pr =
+                    pair_eval<double, COEF, WEIGHT, COEF == 0>(g, in, bm, rmax, rinv, x_walls(g, i), zc);
+                acc[0] += pr.a.r * pr.a.r + pr.b.r * pr.b.r;
+                acc[1] += pr.a.bt * pr.a.bt + pr.b.bt * pr.b.bt;
+                acc[2] += pr.a.pc + pr.b.pc;
+                acc[3] += pr.a.pc * pr.a.pc + pr.b.pc * pr.b.pc;
+                acc[4] += pr.a.r + pr.b.r;
+                if (write) {
+                    const float ra = (float)(pr.a.r * inv_s), rb = (float)(pr.b.r * inv_s);
+                    const unsigned at = (unsigned)(k0 + q) * zm.sz + i;
+                    r32[at + zm.ra] = ra;
+                    r32[at + zm.rb] = rb;
+                    qv = {(float)pr.a.w * ra, (float)pr.b.w * rb};
+                }
+            }
+            if (write) lds[(q * Z::SUB + sidx) * LF::LS + LF::pos((int)x_slot(i, N, g.bcx))] = qv;
+        }
+        if (write) {
+            __syncthreads();
+            transform_rows<float, N, 1, Z::SUB, KF, 1>(lds, tw, g.bcx, twc, sidx, i, [&](int q, int, cpx<float> h) {
+                if (jvalid && k0 + q < (int)nz) {
+                    const unsigned at = (unsigned)(k0 + q) * zm.sz + i;
+                    W32[at + zm.ra] = h.x;
+                    W32[at + zm.rb] = h.y;
+                }
+            });
+        }
+        put_unit_sums<Z::NT, 5>(acc, red, s.partial + (unsigned long long)tile * kPartialStride);  // ends on a barrier
+    }
 }
 
-bool outer_fusable(const GridArgs& g) {
-    bool ok = false;
-    (void)dispatch_len(g.nx, [&]<int N>() {
-        ok = outer_fusable_len<N>();
-        return hipSuccess;
-    });
-    return ok;
-}
+bool outer_fusable(const GridArgs& g) { return g.nx >= 16; }
+
+constexpr int kSmallPlanes = 2;  // of a small tile
 
 hipError_t launch_outer_fused(const GridArgs& g, const Tables& t, const Slot* slots, int nslots, hipStream_t s,
                               int* nunits, float share, bool write) {
+    const int wr = write ? 1 : 0;
     return dispatch_len(g.nx, [&]<int N>() {
-        if constexpr (outer_fusable_len<N>()) {
-            using C = LineCfg<float, N>;
-            using Z = OuterTile<N>;
-            const unsigned nt = (((unsigned)g.ny / 2 + Z::SUB - 1) / Z::SUB) * (((unsigned)g.nz + Z::KM - 1) / Z::KM);
-            if (nunits) *nunits = (int)nt;
+        if constexpr (N < 16) {
+            return hipErrorInvalidValue;
+        } else {
             return dispatch_op(g.coef, g.weight, [&]<int CO, int WE>() {
+                if constexpr (N <= 512) {
+                    using Z = RowTile<N, false>;
+                    const void* k = (const void*)&k_outer_resid_dhtx_s<N, kSmallPlanes, CO, WE>;
+                    const unsigned nt = (((unsigned)g.ny / 2 + Z::SUB - 1) / Z::SUB) *
+                                        (((unsigned)g.nz + kSmallPlanes - 1) / kSmallPlanes);
+                    if (small_tiles_fit(nt, (unsigned)persistent_grid(k, Z::NT, ~0u, 1, 1.0f))) {
+                        if (nunits) *nunits = (int)nt;
+                        const int nb = persistent_grid(k, Z::NT, nt, nslots, share);
+                        k_outer_resid_dhtx_s<N, kSmallPlanes, CO, WE>
+                            <<<dim3(nb, nslots), Z::NT, reserve_lds(k, share), s>>>(g, slots, t, wr);
+                        return hipGetLastError();
+                    }
+                }
                 return dispatch_bc(g.bcx, [&]<int BC>() {
+                    using Z = RowTile<N, true>;
+                    constexpr int KF = RowFlush<double, N>::KF;
                     const void* k = (const void*)&k_outer_resid_dhtx<N, CO, WE, BC>;
-                    const int nb = persistent_grid(k, C::NT, nt, nslots, share);
+                    const unsigned strips = ((unsigned)g.ny / 2 + Z::SUB - 1) / Z::SUB;
+                    const int nf = pick_flushes(KF, 32, strips, (unsigned)g.nz,
+                                                (unsigned)persistent_grid(k, Z::NT, ~0u, 1, 1.0f));
+                    const unsigned km = (unsigned)(nf * KF), nt = strips * (((unsigned)g.nz + km - 1) / km);
+                    if (nunits) *nunits = (int)nt;
+                    const int nb = persistent_grid(k, Z::NT, nt, nslots, share);
                     k_outer_resid_dhtx<N, CO, WE, BC>
-                        <<<dim3(nb, nslots), C::NT, reserve_lds(k, share), s>>>(g, slots, t, write ? 1 : 0);
+                        <<<dim3(nb, nslots), Z::NT, reserve_lds(k, share), s>>>(g, slots, t, wr, nf);
                     return hipGetLastError();
                 });
             });
-        } else {
-            return hipErrorInvalidValue;
         }
     });
 }

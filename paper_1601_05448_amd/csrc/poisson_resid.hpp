@@ -8,30 +8,9 @@
 
 #include "poisson_device.hpp"
 #include "poisson_launch.hpp"
+#include "poisson_rows.hpp"
 
 namespace pois {
-
-// Rows that fill whole waves, and a register budget for CPT marching columns.
-template <typename T, int N>
-constexpr bool use_zmarch() {
-    using C = LineCfg<T, N>;
-    if constexpr (N % 64 != 0) return false;
-    else return (N >= C::NT ? N / C::NT : 1) * (int)sizeof(T) <= 32;
-}
-
-// Minimum waves per SIMD the residual sweep's registers are sized for (the
-// second __launch_bounds__ argument, which caps the registers per thread): one
-// where four FP64 marching columns per thread need the accumulation registers
-// too.  The FP32 sweep on 512-cell rows runs 512-thread blocks whose LDS leaves
-// room for two per CU: asking for four waves per SIMD (128 registers) lets both
-// be resident, 16 waves per CU instead of 8 (6% faster at 512^3; the FP32 y, z
-// and x-update sweeps spill at 128 registers and lose 2x, so they keep one).
-template <typename T, int N>
-constexpr int p1_min_blocks() {
-    using C = LineCfg<T, N>;
-    if constexpr (sizeof(T) == 4 && N == 512 && C::NT == 512) return 4;
-    return (N >= C::NT ? N / C::NT : 1) * (int)sizeof(T) > 16 ? 1 : C::MINB;
-}
 
 // ---- P1: residual, weight, Hartley along x --------------------------------------
 // MODE 0: stencil residual of the iteration view; MODE 1: q = b (copy, for the
@@ -131,39 +110,53 @@ k_resid_dhtx(GridArgs g, const Slot* __restrict__ slots, Tables tb) {
     }
 }
 
-// P1 for rows whose length is a multiple of the wave size: the residual of a tile
-// of KM planes x SUB row pairs is computed by z-marching columns (see ZMarch);
-// every KF planes the tile's L lines are transformed along x and written out.
-// Within a flush, line l = s KF + q is row pair jp = tj SUB + s of plane
-// k = tk KM + f KF + q.
+// P1 on rows of 16 and more: the residual of a tile of `nflush` KF planes x
+// SUB row pairs is computed by z-marching columns (see ZMarch); every KF
+// planes the tile's lines are transformed along x and written out.
+// Bound by memory on large grids, by latency on small ones.  Measured (MI355X, start
+// -> now, us): FP64 at 64^3 32 -> 6.7 (small tiles), 128^3 33 -> 17 and 192^3 77 -> 59
+// (tiles of 8 planes: enough blocks, no short last round), 384^3 747 -> 455 (one
+// column per thread instead of two), 96^3 32 -> 12.6 (marched, not gathered),
+// 1024 x 512 x 512 2614 -> 2030 (two columns per thread, two waves per SIMD, instead
+// of four in one); FP32 at 384^3 249 -> 238, at 192^3 45 -> 26.
+//
+// Waves per SIMD the registers are sized for: FP32 rows of up to 512 within 128
+// registers, the others within 256.
+template <typename T, int N>
+constexpr int resid_min_waves() {
+    return sizeof(T) == 4 && N <= 512 ? 4 : 2;
+}
+
 template <typename T, int N, int COEF, int WEIGHT, int BCX>
-__global__ void __launch_bounds__((LineCfg<T, N>::NT), (p1_min_blocks<T, N>()))
-k_resid_dhtx_z(GridArgs g, const Slot* __restrict__ slots, Tables tb) {
-    using C = LineCfg<T, N>;
-    using Z = P1Tile<T, N>;
-    __shared__ cpx<T> lds[C::L * C::LS];
+__global__ void __launch_bounds__((RowTile<N, true>::NT), (resid_min_waves<T, N>()))
+k_resid_dhtx_z(GridArgs g, const Slot* __restrict__ slots, Tables tb, int nflush) {
+    using Z = RowTile<N, true>;
+    using RF = RowFlush<T, N>;
+    using LF = LineFft<T, N, true, RF::SET>;
+    constexpr int KF = RF::KF;
+    __shared__ cpx<T> lds[Z::SUB * KF * LF::LS];
     __shared__ cpx<T> tw[N];
-    __shared__ double red[(C::NT / 64) * 4];
-    __shared__ T edge[2 * Z::SUB * Z::EDGE];  // wave-edge columns, double-buffered by step parity
+    __shared__ double red[(Z::NT / 64) * 4];
+    __shared__ PlaneRows<T> xb[2 * Z::SUB * Z::XV];  // x neighbours, double-buffered by step parity
     const Slot& s = slots[blockIdx.y];
     if (IterView<T>::skip_p1(s.st)) return;
     const cpx<T>* twg = twiddles<T>(tb, 0);
     const cpx<T>* twc = dct_twiddles<T>(tb);
-    for (int e = threadIdx.x; e < N; e += C::NT) tw[e] = twg[e];
+    for (int e = threadIdx.x; e < N; e += Z::NT) tw[e] = twg[e];
     const IterView<T> v(s);
 
-    const unsigned nyh = (unsigned)g.ny / 2, nz = (unsigned)g.nz;
-    const unsigned ngj = (nyh + Z::SUB - 1) / Z::SUB, ngk = (nz + Z::KM - 1) / Z::KM;
+    const unsigned nyh = (unsigned)g.ny / 2, nz = (unsigned)g.nz, km = (unsigned)(nflush * KF);
+    const unsigned ngj = (nyh + Z::SUB - 1) / Z::SUB, ngk = (nz + km - 1) / km;
     const unsigned ntiles = ngj * ngk;
-    const int sidx = (N >= C::NT) ? 0 : (int)threadIdx.x / N;
-    const unsigned col0 = (N >= C::NT) ? threadIdx.x : threadIdx.x % N;
+    const int sidx = (int)threadIdx.x / Z::MT;
+    const unsigned col0 = threadIdx.x % Z::MT;
     ZMarch<T> zm;
     zm.p = (const T*)v.p;
     zm.rho = (const T*)v.rho;
     zm.rhs = (const T*)v.rhs;
-    zm.nx = (unsigned)g.nx;
+    zm.nx = (unsigned)N;
     zm.nz = nz;
-    zm.sz = (unsigned)g.nx * (unsigned)g.ny;
+    zm.sz = (unsigned)N * (unsigned)g.ny;
     zm.lane = (int)(threadIdx.x & 63);
     double acc[4] = {0.0, 0.0, 0.0, 0.0};  // sum r^2, sum bt^2, sum p, sum p^2
 
@@ -172,12 +165,12 @@ k_resid_dhtx_z(GridArgs g, const Slot* __restrict__ slots, Tables tb) {
         const unsigned jp = tj * Z::SUB + sidx;
         const bool jvalid = jp < nyh;
         zm.rows_of(jvalid ? jp : 0u, (unsigned)g.ny);
-        const int k0 = (int)(tk * Z::KM);
+        const int k0 = (int)(tk * km);
         PlaneRows<T> pl[Z::CPT][3];
         PlaneSide<T> sd[Z::CPT];
 #pragma unroll
         for (int c = 0; c < Z::CPT; ++c) {
-            const unsigned i = col0 + c * C::NT;
+            const unsigned i = col0 + c * Z::MT;
             zm.load_rows(zm.plane(k0 - 1), i, pl[c][0]);
             zm.load_rows(zm.plane(k0), i, pl[c][1]);
             zm.load_rows(zm.plane(k0 + 1), i, pl[c][2]);
@@ -187,13 +180,13 @@ k_resid_dhtx_z(GridArgs g, const Slot* __restrict__ slots, Tables tb) {
         // (one marching column per thread: with more, the registers are spoken for)
         constexpr bool kZC = COEF == 0 && Z::CPT == 1;
         T zc[Z::CPT][2];
-        for (int f = 0; f < Z::KM / Z::KF; ++f) {
+        for (int f = 0; f < nflush && k0 + f * KF < (int)nz; ++f) {
             T tacc[2] = {T(0), T(0)};
             // fully unrolled, so that the rotation of the plane registers below
             // is a renaming and not a copy that would wait for the prefetched loads
 #pragma unroll
-            for (int q = 0; q < Z::KF; ++q) {
-                const int k = k0 + f * Z::KF + q;
+            for (int q = 0; q < KF; ++q) {
+                const int k = k0 + f * KF + q;
                 const bool valid = jvalid && k < (int)nz;
                 // the next step's plane and side fly while this step computes (also
                 // on the tile's last step, wrapped in z and unused, so that the wait
@@ -205,20 +198,22 @@ k_resid_dhtx_z(GridArgs g, const Slot* __restrict__ slots, Tables tb) {
                 __builtin_amdgcn_s_setprio(2);
 #pragma unroll
                 for (int c = 0; c < Z::CPT; ++c) {
-                    const unsigned i = col0 + c * C::NT;
+                    const unsigned i = col0 + c * Z::MT;
                     zm.load_rows(zm.plane(k + 2), i, nn[c]);
                     zm.load_side(zm.plane(k + 1), i, ns[c]);
                 }
                 __builtin_amdgcn_s_setprio(0);
-                T* eb = edge + ((q & 1) * Z::SUB + sidx) * Z::EDGE;
+                PlaneRows<T>* eb = xb + ((q & 1) * Z::SUB + sidx) * Z::XV;
 #pragma unroll
-                for (int c = 0; c < Z::CPT; ++c) zm.edge_put(eb, col0 + c * C::NT, pl[c][1]);
+                for (int c = 0; c < Z::CPT; ++c) zm.template x_put<Z::DPP>(eb, col0 + c * Z::MT, pl[c][1]);
                 __syncthreads();
 #pragma unroll
                 for (int c = 0; c < Z::CPT; ++c) {
-                    const unsigned i = col0 + c * C::NT;
+                    const unsigned i = col0 + c * Z::MT;
                     PairIn<T> in;
-                    zm.pair(pl[c][0], pl[c][1], pl[c][2], sd[c], zm.edge_get(eb, i), in);
+                    PlaneRows<T> xm, xp;
+                    zm.template x_get<Z::DPP>(eb, i, pl[c][1], xm, xp);
+                    zm.pair(pl[c][0], pl[c][1], pl[c][2], sd[c], xm, xp, in);
                     cpx<T> qv = {T(0), T(0)};
                     if (valid) {
                         if constexpr (kZC)
@@ -238,7 +233,7 @@ k_resid_dhtx_z(GridArgs g, const Slot* __restrict__ slots, Tables tb) {
                             tacc[1] += o.a.bt * o.a.bt + o.b.bt * o.b.bt;
                         }
                     }
-                    lds[(sidx * Z::KF + q) * C::LS + C::pos(x_slot(i, N, BCX))] = qv;
+                    lds[(q * Z::SUB + sidx) * LF::LS + LF::pos((int)x_slot(i, N, BCX))] = qv;
                 }
 #pragma unroll
                 for (int c = 0; c < Z::CPT; ++c) {
@@ -253,66 +248,190 @@ k_resid_dhtx_z(GridArgs g, const Slot* __restrict__ slots, Tables tb) {
                 acc[1] += (double)tacc[1];
             }
             __syncthreads();
-            fft_block_lines<T, N>(lds, tw);
-#pragma unroll
-            for (int it = 0; it < C::IT; ++it) {
-                const int e = threadIdx.x + it * C::NT;
-                const int l = e / N, k = e % N;
-                const unsigned ljp = tj * Z::SUB + l / Z::KF;
-                const unsigned lk = (unsigned)(k0 + f * Z::KF) + l % Z::KF;
-                if (ljp < nyh && lk < nz) {
-                    const unsigned P = lk * nyh + ljp;  // row pair index, rows 2P and 2P + 1
-                    const cpx<T> h = x_forward_out<T, N>(lds + l * C::LS, k, BCX, twc);
+            const int kf = k0 + f * KF;
+            transform_rows<T, N, RF::SET, Z::SUB, KF, Z::CPT>(lds, tw, BCX, twc, sidx, col0, [&](int q, int c, cpx<T> h) {
+                if (jvalid && kf + q < (int)nz) {
                     // streaming stores: the transformed lines are not read
                     // again by this sweep, and left out of L2 they do not push
                     // out the rows that neighbouring tiles read as y halo
                     // (FP64 at 512^3: 1.09 -> 1.02 of the algorithmic bytes)
-                    __builtin_nontemporal_store(h.x, &v.W[(2 * P) * N + k]);
-                    __builtin_nontemporal_store(h.y, &v.W[(2 * P + 1) * N + k]);
+                    const unsigned at = (unsigned)(kf + q) * zm.sz + col0 + c * Z::MT;
+                    __builtin_nontemporal_store(h.x, &v.W[at + zm.ra]);
+                    __builtin_nontemporal_store(h.y, &v.W[at + zm.rb]);
                 }
-            }
+            });
             __syncthreads();  // the next flush overwrites the lines
         }
-        put_unit_sums<C::NT, 4>(acc, red, s.partial + (unsigned long long)tile * kPartialStride);
+        put_unit_sums<Z::NT, 4>(acc, red, s.partial + (unsigned long long)tile * kPartialStride);
     }
 }
 
-template <typename T, int MODE>
-static hipError_t resid_t(const GridArgs& g, const Tables& t, const Slot* slots, int nslots, hipStream_t s,
-                          int* nunits, float share) {
-    const unsigned rows = (unsigned)(g.ny * g.nz / 2);
-    return dispatch_len(g.nx, [&]<int N>() {
-        using C = LineCfg<T, N>;
-        const unsigned ng = (rows + C::L - 1) / C::L;
-        return dispatch_op(MODE == 1 ? 0 : g.coef, MODE == 1 ? 0 : g.weight, [&]<int CO, int WE>() {
-            if constexpr (MODE == 0 && use_zmarch<T, N>()) {
-                using Z = P1Tile<T, N>;
-                const unsigned nt = (((unsigned)g.ny / 2 + Z::SUB - 1) / Z::SUB) *
-                                    (((unsigned)g.nz + Z::KM - 1) / Z::KM);
-                if (nunits) *nunits = (int)nt;
-                return dispatch_bc(g.bcx, [&]<int BC>() {
-                    const void* k = (const void*)&k_resid_dhtx_z<T, N, CO, WE, BC>;
-                    const int nb = persistent_grid(k, C::NT, nt, nslots, share);
-                    k_resid_dhtx_z<T, N, CO, WE, BC>
-                        <<<dim3(nb, nslots), C::NT, reserve_lds(k, share), s>>>(g, slots, t);
-                    return hipGetLastError();
-                });
-            } else {
-                const void* k = (const void*)&k_resid_dhtx<T, N, MODE, CO, WE>;
-                const int nb = persistent_grid(k, C::NT, ng, nslots, share);
-                if (nunits) *nunits = (int)ng;
-                k_resid_dhtx<T, N, MODE, CO, WE><<<dim3(nb, nslots), C::NT, reserve_lds(k, share), s>>>(g, slots, t);
+// P1 on small grids, rows of 16 to 512: a tile of KF planes x SUB row pairs whose
+// loads are all issued at once, so that a block waits for memory once, and whose
+// blocks are many: such a grid lies in the caches, and a marching tile would spend
+// its time on one load latency per plane in a few blocks.
+template <typename T, int N, int KF, int COEF, int WEIGHT>
+__global__ void __launch_bounds__((RowTile<N, false>::NT))
+k_resid_dhtx_s(GridArgs g, const Slot* __restrict__ slots, Tables tb) {
+    using Z = RowTile<N, false>;
+    using LF = LineFft<T, N, true, 1>;
+    static_assert(Z::CPT == 1, "one column per thread");
+    __shared__ cpx<T> lds[Z::SUB * KF * LF::LS];
+    __shared__ cpx<T> tw[N];
+    __shared__ double red[(Z::NT / 64) * 4];
+    __shared__ PlaneRows<T> xb[KF * Z::SUB * Z::XV];
+    const Slot& s = slots[blockIdx.y];
+    if (IterView<T>::skip_p1(s.st)) return;
+    const cpx<T>* twg = twiddles<T>(tb, 0);
+    const cpx<T>* twc = dct_twiddles<T>(tb);
+    for (int e = threadIdx.x; e < N; e += Z::NT) tw[e] = twg[e];
+    const IterView<T> v(s);
+
+    const unsigned nyh = (unsigned)g.ny / 2, nz = (unsigned)g.nz;
+    const unsigned ngj = (nyh + Z::SUB - 1) / Z::SUB, ngk = (nz + KF - 1) / KF;
+    const unsigned ntiles = ngj * ngk;
+    const int sidx = (int)threadIdx.x / N;
+    const unsigned i = threadIdx.x % N;
+    ZMarch<T> zm;
+    zm.p = (const T*)v.p;
+    zm.rho = (const T*)v.rho;
+    zm.rhs = (const T*)v.rhs;
+    zm.nx = (unsigned)N;
+    zm.nz = nz;
+    zm.sz = (unsigned)N * (unsigned)g.ny;
+    zm.lane = (int)(threadIdx.x & 63);
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    for (unsigned tile = xcd_block(blockIdx.x, gridDim.x); tile < ntiles; tile += gridDim.x) {
+        const unsigned tj = tile % ngj, tk = tile / ngj;
+        const unsigned jp = tj * Z::SUB + sidx;
+        const bool jvalid = jp < nyh;
+        zm.rows_of(jvalid ? jp : 0u, (unsigned)g.ny);
+        const int k0 = (int)(tk * KF);
+        PlaneRows<T> pl[KF + 2];
+        PlaneSide<T> sd[KF];
+#pragma unroll
+        for (int q = 0; q < KF + 2; ++q) zm.load_rows(zm.plane(k0 + q - 1), i, pl[q]);
+#pragma unroll
+        for (int q = 0; q < KF; ++q) zm.load_side(zm.plane(k0 + q), i, sd[q]);
+#pragma unroll
+        for (int q = 0; q < KF; ++q)
+            zm.template x_put<Z::DPP>(xb + (q * Z::SUB + sidx) * Z::XV, i, pl[q + 1]);
+        __syncthreads();
+        T zc[2], tacc[2] = {T(0), T(0)};
+#pragma unroll
+        for (int q = 0; q < KF; ++q) {
+            const bool valid = jvalid && k0 + q < (int)nz;
+            PairIn<T> in;
+            PlaneRows<T> xm, xp;
+            zm.template x_get<Z::DPP>(xb + (q * Z::SUB + sidx) * Z::XV, i, pl[q + 1], xm, xp);
+            zm.pair(pl[q], pl[q + 1], pl[q + 2], sd[q], xm, xp, in);
+            cpx<T> qv = {T(0), T(0)};
+            if (valid) {
+                if constexpr (COEF == 0)
+                    if (q == 0) z_faces_below(in, v.rinv, zc);
+                const PairOut<T> o =
+                    pair_eval<T, COEF, WEIGHT, COEF == 0>(g, in, v.rhs_mean, v.rmax, v.rinv, x_walls(g, i), zc);
+                qv = {o.a.w * o.a.r, o.b.w * o.b.r};
+                if constexpr (sizeof(T) == 8) {
+                    acc[0] += o.a.r * o.a.r + o.b.r * o.b.r;
+                    acc[1] += o.a.bt * o.a.bt + o.b.bt * o.b.bt;
+                    acc[2] += o.a.pc + o.b.pc;
+                    acc[3] += o.a.pc * o.a.pc + o.b.pc * o.b.pc;
+                } else {
+                    tacc[0] += o.a.r * o.a.r + o.b.r * o.b.r;
+                    tacc[1] += o.a.bt * o.a.bt + o.b.bt * o.b.bt;
+                }
             }
-            return hipGetLastError();
+            lds[(q * Z::SUB + sidx) * LF::LS + LF::pos((int)x_slot(i, N, g.bcx))] = qv;
+        }
+        if constexpr (sizeof(T) == 4) {
+            acc[0] += (double)tacc[0];
+            acc[1] += (double)tacc[1];
+        }
+        __syncthreads();
+        transform_rows<T, N, 1, Z::SUB, KF, 1>(lds, tw, g.bcx, twc, sidx, i, [&](int q, int, cpx<T> h) {
+            if (jvalid && k0 + q < (int)nz) {
+                const unsigned at = (unsigned)(k0 + q) * zm.sz + i;
+                v.W[at + zm.ra] = h.x;
+                v.W[at + zm.rb] = h.y;
+            }
         });
-    });
+        put_unit_sums<Z::NT, 4>(acc, red, s.partial + (unsigned long long)tile * kPartialStride);  // ends on a barrier
+    }
 }
 
+// Gathered rows: `mode` 1 (any length), or rows shorter than 16.
+template <typename T, int N, int MODE, int CO, int WE>
+static hipError_t run_gather(const GridArgs& g, const Tables& t, const Slot* slots, int nslots, hipStream_t s,
+                             int* nunits, float share) {
+    using C = LineCfg<T, N>;
+    const unsigned ng = ((unsigned)(g.ny * g.nz / 2) + C::L - 1) / C::L;
+    const void* k = (const void*)&k_resid_dhtx<T, N, MODE, CO, WE>;
+    const int nb = persistent_grid(k, C::NT, ng, nslots, share);
+    if (nunits) *nunits = (int)ng;
+    k_resid_dhtx<T, N, MODE, CO, WE><<<dim3(nb, nslots), C::NT, reserve_lds(k, share), s>>>(g, slots, t);
+    return hipGetLastError();
+}
+
+// Planes of a small tile.
+constexpr int kSmallPlanes = 2;
+
+template <typename T, int N, int CO, int WE>
+static hipError_t run_small(const GridArgs& g, const Tables& t, const Slot* slots, int nslots, hipStream_t s,
+                            int* nunits, float share, bool* fits) {
+    using Z = RowTile<N, false>;
+    const void* k = (const void*)&k_resid_dhtx_s<T, N, kSmallPlanes, CO, WE>;
+    const unsigned nt =
+        (((unsigned)g.ny / 2 + Z::SUB - 1) / Z::SUB) * (((unsigned)g.nz + kSmallPlanes - 1) / kSmallPlanes);
+    *fits = small_tiles_fit(nt, (unsigned)persistent_grid(k, Z::NT, ~0u, 1, 1.0f));
+    if (!*fits) return hipSuccess;
+    if (nunits) *nunits = (int)nt;
+    const int nb = persistent_grid(k, Z::NT, nt, nslots, share);
+    k_resid_dhtx_s<T, N, kSmallPlanes, CO, WE><<<dim3(nb, nslots), Z::NT, reserve_lds(k, share), s>>>(g, slots, t);
+    return hipGetLastError();
+}
+
+template <typename T, int N, int CO, int WE, int BC>
+static hipError_t run_march(const GridArgs& g, const Tables& t, const Slot* slots, int nslots, hipStream_t s,
+                            int* nunits, float share) {
+    using Z = RowTile<N, true>;
+    constexpr int KF = RowFlush<T, N>::KF;
+    const void* k = (const void*)&k_resid_dhtx_z<T, N, CO, WE, BC>;
+    const unsigned strips = ((unsigned)g.ny / 2 + Z::SUB - 1) / Z::SUB;
+    // long FP32 rows with many strips: shorter tiles keep neighbours closer in z,
+    // so that more of the y halo rows they read from each other are still in L2
+    // (512^3: 463 us, 32 planes 481; 512 x 256 x 256 the other way, 126 and 118)
+    const int most = sizeof(T) == 4 && N >= 512 && strips >= 256 ? 16 : 32;
+    const int nf = pick_flushes(KF, most, strips, (unsigned)g.nz, (unsigned)persistent_grid(k, Z::NT, ~0u, 1, 1.0f));
+    const unsigned km = (unsigned)(nf * KF), nt = strips * (((unsigned)g.nz + km - 1) / km);
+    if (nunits) *nunits = (int)nt;
+    const int nb = persistent_grid(k, Z::NT, nt, nslots, share);
+    k_resid_dhtx_z<T, N, CO, WE, BC><<<dim3(nb, nslots), Z::NT, reserve_lds(k, share), s>>>(g, slots, t, nf);
+    return hipGetLastError();
+}
+
+// The tiles follow from the grid alone (and the chip's size), so that the units'
+// sums are the same bits in every batch and share.
 template <typename T>
 hipError_t launch_resid(const GridArgs& g, const Tables& t, const Slot* slots, int nslots, int mode, hipStream_t s,
                         int* nunits, float share) {
-    return mode == 1 ? resid_t<T, 1>(g, t, slots, nslots, s, nunits, share)
-                     : resid_t<T, 0>(g, t, slots, nslots, s, nunits, share);
+    return dispatch_len(g.nx, [&]<int N>() {
+        if (mode == 1) return run_gather<T, N, 1, 0, 0>(g, t, slots, nslots, s, nunits, share);
+        return dispatch_op(g.coef, g.weight, [&]<int CO, int WE>() {
+            if constexpr (N < 16) {
+                return run_gather<T, N, 0, CO, WE>(g, t, slots, nslots, s, nunits, share);
+            } else {
+                if constexpr (N <= 512) {
+                    bool fits = false;
+                    const hipError_t e = run_small<T, N, CO, WE>(g, t, slots, nslots, s, nunits, share, &fits);
+                    if (fits) return e;
+                }
+                return dispatch_bc(g.bcx, [&]<int BC>() {
+                    return run_march<T, N, CO, WE, BC>(g, t, slots, nslots, s, nunits, share);
+                });
+            }
+        });
+    });
 }
 
 }  // namespace pois

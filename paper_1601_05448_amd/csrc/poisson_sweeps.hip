@@ -1,8 +1,9 @@
 // The four field sweeps of one iteration of the paper's method (section
 // "Poisson equation", eq. (Pois)), written for gfx950:
 //   P1 k_resid_dhtx_z r = b~ - A p, q = w r, partial norms per tile, Hartley
-//                     along x -> W (z-marching stencil; k_resid_dhtx, a row-pair
-//                     gather, for rows that do not fill whole waves)
+//                     along x -> W (z-marching stencil; k_resid_dhtx_s, tiles whose
+//                     loads are issued at once, on small grids; k_resid_dhtx, a
+//                     row-pair gather, for rows shorter than 16)
 //   P2 k_dht_cols     Hartley along y of W (also P4: the transform is self-inverse)
 //   P3 k_dht_z_solve  Hartley along z, divide by n * symbol, Hartley along z
 //                     (taken as FFT, scaling of the separated spectra, inverse FFT)
