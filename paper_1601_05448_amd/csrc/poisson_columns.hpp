@@ -46,7 +46,6 @@ constexpr int narrow_lines() {
     constexpr int tt = FftPlan<N>::TT, run = sizeof(T) == 8 || tt >= 64 ? 8 : 16;
     return 64 / tt > run ? 64 / tt : run;
 }
-constexpr unsigned kWideGroups = 512;
 
 template <typename T, int N, int L>
 struct ColShape {

@@ -13,6 +13,10 @@ int persistent_grid(const void* kernel, int threads, unsigned ngroups, int nslot
 // (a share of at most one half), else 0.
 unsigned reserve_lds(const void* kernel, float share);
 
+// A line sweep takes its wide blocks where they make at least this many groups:
+// two blocks per CU.
+constexpr unsigned kWideGroups = 512;
+
 // One sweep each, MODE as in launch_sweep_mode.  The type selects the FP64 or
 // FP32 fields of the slots.
 template <typename T>
