@@ -1,14 +1,12 @@
 // Convergence control of the iteration: the decisions taken on the device
-// after each residual evaluation, and the fused hand-off that runs them.
+// after each residual evaluation.
 //
 // A sweep that evaluates a residual writes one set of partial sums per unit of
 // work (a z-marching tile or a line group), in the unit's own slot of the
 // solve's partial array, so that the sums do not depend on how many blocks the
 // launch had (a solve gives the same bits alone and in a batch, whatever share
-// of the chip its launches get).  A one-block kernel per solve then adds the
-// units' sums in a fixed order and takes the decision.  (Taking it in the
-// sweep's last block instead needs a device-scope fence in every block, which
-// on this chip writes back the XCD's L2 and costs far more than the launch.)
+// of the chip its launches get).  The launch's last block then adds the units'
+// sums in a fixed order and takes the decision (last_block).
 #pragma once
 
 #include "poisson_device.hpp"
@@ -127,15 +125,6 @@ __device__ inline void decide_outer(const GridArgs& g, SolveState* st, const dou
 // FP32_REFINE, after the FP32 P1 of an inner iteration.  sums: r^2, bt^2.
 __device__ inline void decide_inner(SolveState* st, const double* sums, int max_inner) {
     const int t = st->inner_iter;
-    if (st->stop_next) {
-        // the previous iteration was predicted to be the phase's last: its
-        // update has been applied and this iteration's P1 idled
-        st->stop_next = 0;
-        st->inner_done = 1;
-        st->inner_last = t + 1;
-        st->stage = 2;
-        return;
-    }
     st->p1_work += 1;  // P1 did its work
     if (t == 0) st->rhs_norm32 = sqrt(sums[1]);
     const double rel = (st->rhs_norm32 > 0.0) ? sqrt(sums[0]) / st->rhs_norm32 : 0.0;
@@ -178,6 +167,15 @@ __device__ inline void decide_inner(SolveState* st, const double* sums, int max_
             }
         }
     }
+}
+
+// FP32_REFINE, the end of an inner phase whose last iteration was predicted: its
+// update has been applied, and no evaluation follows.
+__device__ inline void close_inner(SolveState* st) {
+    st->stop_next = 0;
+    st->inner_done = 1;
+    st->inner_last = st->inner_iter + 1;
+    st->stage = 2;
 }
 
 }  // namespace pois

@@ -469,15 +469,76 @@ __device__ __forceinline__ void block_sums(double (&v)[K], double* red) {
     }
 }
 
+// ---- hand-over to a launch's last block -------------------------------------------
+// A launch that ends in a decision takes it in the block that arrives last at the
+// solve's counter (SolveState::arrive), which adds the other blocks' sums.  The
+// sums travel by agent-scope atomic stores and loads, which pass the XCDs' L2s by,
+// each block waits for its stores before it arrives, and nothing else is handed
+// over; so no block needs a device-scope fence, which would write its XCD's L2
+// back (the fence made P1 50% slower; a kernel of its own for the decision took
+// 5 us and a launch gap per iteration).
+
+__device__ __forceinline__ void put_shared(double* p, double v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double get_shared(const double* p) {
+    return __hip_atomic_load(const_cast<double*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Counters of the arriving blocks: one atomic on an address takes some 10 ns, which
+// a thousand blocks on one address would feel (P1 at 192^3 in FP32 by 14 us), so the
+// blocks arrive at kArriveGroups counters, and the last of each group at the
+// solve's.  A group's counter is the last, otherwise unused, word of a set of
+// partial sums, kArriveStep sets from the next group's.
+__device__ __forceinline__ unsigned* arrive_group(double* partial, unsigned group) {
+    return reinterpret_cast<unsigned*>(partial + (unsigned long long)group * (kArriveStep * kPartialStride) +
+                                       (kPartialStride - 1));
+}
+
+__device__ __forceinline__ bool last_to_arrive(unsigned* counter, unsigned expected) {
+    const unsigned before = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (before + 1u != expected) return false;
+    __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // for the next launch
+    return true;
+}
+
+// Every thread of the block calls it once, after the block's last put_shared (by
+// thread 0) and its last read of the solve's state.  True in the last of the
+// gridDim.x blocks of the launch for this solve.
+__device__ __forceinline__ bool last_block(const Slot& s) {
+    __shared__ int last;
+    if (threadIdx.x == 0) {
+        __builtin_amdgcn_s_waitcnt(0);  // this thread's stores have reached memory
+        const unsigned nb = gridDim.x, group = blockIdx.x % kArriveGroups;
+        const unsigned groups = nb < kArriveGroups ? nb : kArriveGroups;
+        last = last_to_arrive(arrive_group(s.partial, group), (nb - group + kArriveGroups - 1) / kArriveGroups) &&
+               last_to_arrive(&s.st->arrive, groups);
+    }
+    __syncthreads();
+    return last != 0;
+}
+
 // Units' K sums, added by the NT threads of a block in a fixed order; the total
-// is in out[] of thread 0.
+// is in out[] of thread 0.  Eight units' loads are in flight per thread.
 template <int NT, int K>
 __device__ __forceinline__ void sum_units(const double* part, unsigned n, double (&out)[K], double* red) {
+    constexpr unsigned kU = 8;
 #pragma unroll
     for (int q = 0; q < K; ++q) out[q] = 0.0;
-    for (unsigned u = threadIdx.x; u < n; u += NT)
+    for (unsigned u0 = threadIdx.x; u0 < n; u0 += kU * NT) {
+        double v[kU][K];
 #pragma unroll
-        for (int q = 0; q < K; ++q) out[q] += part[(unsigned long long)u * kPartialStride + q];
+        for (unsigned b = 0; b < kU; ++b) {
+            const unsigned u = u0 + b * NT;
+            const double* at = part + (unsigned long long)(u < n ? u : u0) * kPartialStride;
+#pragma unroll
+            for (int q = 0; q < K; ++q) v[b][q] = get_shared(at + q);
+        }
+#pragma unroll
+        for (unsigned b = 0; b < kU; ++b)
+#pragma unroll
+            for (int q = 0; q < K; ++q) out[q] += u0 + b * NT < n ? v[b][q] : 0.0;
+    }
     block_sums<NT, K>(out, red);
 }
 
@@ -487,7 +548,7 @@ __device__ __forceinline__ void put_unit_sums(double (&v)[K], double* red, doubl
     block_sums<NT, K>(v, red);
     if (threadIdx.x == 0)
 #pragma unroll
-        for (int q = 0; q < K; ++q) dst[q] = v[q];
+        for (int q = 0; q < K; ++q) put_shared(dst + q, v[q]);
 #pragma unroll
     for (int q = 0; q < K; ++q) v[q] = 0.0;
     __syncthreads();  // red is reused by the next unit
@@ -522,13 +583,10 @@ struct IterView<float> {
     static __device__ bool skip(const SolveState* st, int stage = 1) {
         return st->done != 0 || st->stage != stage || st->inner_done != 0;
     }
-    // the inner residual sweep also idles once the phase is known to end after
-    // the iteration in progress (its evaluation is not needed), and while the
-    // update of the last evaluation is still due (a launch sequence may end on
-    // an evaluation and leave that update to the next one)
-    static __device__ bool skip_p1(const SolveState* st) {
-        return skip(st) || st->stop_next != 0 || st->upd_due != 0;
-    }
+    // the inner residual sweep also idles while the update of the last evaluation
+    // is still due (a launch sequence may end on an evaluation and leave that
+    // update to the next one); see p1_idle for a phase known to end (stop_next)
+    static __device__ bool skip_p1(const SolveState* st) { return skip(st) || st->upd_due != 0; }
 };
 
 template <typename T>

@@ -274,7 +274,6 @@ int drive_solve(const GridArgs& g, const Geometry& geo, const Tables& t, const S
         hipSuccess)
         return hip_status(e);
     if ((e = launch_setup(g, geo, d_slots, nslots, fp32, s)) != hipSuccess) return hip_status(e);
-    if ((e = launch_setup_finalize(g, geo, d_slots, nslots, s)) != hipSuccess) return hip_status(e);
     const size_t hb = offsetof(SolveState, hist);
     bool all_done = false;
     auto poll = [&]() -> int {  // 1: all done, 0: not yet, <0 error
@@ -691,7 +690,6 @@ int poisson_residual(poisson_t h, const double* rho, const double* b, const doub
     hipError_t e;
     if ((e = launch_init(h->g, h->d_slot, 1, 1.0, 0, 0, POISSON_FP64, h->stream)) != hipSuccess) return hip_status(e);
     if ((e = launch_setup(h->g, h->geo, h->d_slot, 1, false, h->stream)) != hipSuccess) return hip_status(e);
-    if ((e = launch_setup_finalize(h->g, h->geo, h->d_slot, 1, h->stream)) != hipSuccess) return hip_status(e);
     if ((e = launch_residual(h->g, h->geo, h->d_slot, r, h->stream)) != hipSuccess) return hip_status(e);
     const int nb = h->geo.blocks_pt;
     std::vector<double> part((size_t)nb * kPartialStride);
@@ -721,7 +719,6 @@ int poisson_time_sweep(poisson_t h, int sweep, int fp32, const double* rho, cons
     if ((e = launch_init(h->g, h->d_slot, 1, 0.0, 1 << 30, 1 << 30, h->o.precision, h->stream)) != hipSuccess)
         return hip_status(e);
     if ((e = launch_setup(h->g, h->geo, h->d_slot, 1, fp32 != 0, h->stream)) != hipSuccess) return hip_status(e);
-    if ((e = launch_setup_finalize(h->g, h->geo, h->d_slot, 1, h->stream)) != hipSuccess) return hip_status(e);
     // the inner sweeps run in stage 1, which the outer residual opens; the
     // outer residual sweep itself in stage 0
     if (fp32 && sweep != 6 &&
@@ -729,8 +726,9 @@ int poisson_time_sweep(poisson_t h, int sweep, int fp32, const double* rho, cons
         return hip_status(e);
     auto one = [&]() {
         if (sweep != 6) return launch_sweep(h->g, h->tables.t, h->d_slot, 1, fp32 != 0, sweep, h->stream);
-        return outer_fusable(h->g) ? launch_outer_fused(h->g, h->tables.t, h->d_slot, 1, h->stream, nullptr)
-                                   : launch_outer_resid_sweep(h->g, h->d_slot, 1, h->stream, nullptr);
+        return outer_fusable(h->g)
+                   ? launch_outer_fused(h->g, h->tables.t, h->d_slot, 1, h->stream, 1.0f, true, false)
+                   : launch_outer_resid_sweep(h->g, h->d_slot, 1, h->stream, false);
     };
     if ((e = one()) != hipSuccess) return hip_status(e);  // warm
     if ((e = hipEventRecord(h->ev0, h->stream)) != hipSuccess) return hip_status(e);

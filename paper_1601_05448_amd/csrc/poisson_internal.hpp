@@ -10,6 +10,8 @@ namespace pois {
 constexpr int kHistCap = 256;      // residual-history entries kept per solve
 constexpr int kPartialStride = 8;  // doubles per set of partial sums (one set per block or per unit of work)
 constexpr int kMaxSetupBlocks = 4096;
+constexpr unsigned kArriveGroups = 32;  // counters a launch's blocks arrive at (last_block) ...
+constexpr int kArriveStep = 4;          // ... in every fourth set of partial sums
 constexpr int kStageTail = 3;  // see SolveState::stage
 constexpr int kMaxInnerPerStep = 1 << 20;  // FP32 inner sweeps per refinement step: bounded by max_iter
 
@@ -25,10 +27,11 @@ struct GridArgs {
     int bcx;           // 0 periodic in x; 1 zero-flux walls at both ends of x
 };
 
-// Per-solve state, resident in device memory.  Written only by the one-block
-// finalize kernels (and zeroed by the init kernel); every sweep kernel reads
-// `done` first and returns at once when the solve is over, so that unrolled
-// iteration sequences stop doing work after convergence.
+// Per-solve state, resident in device memory.  Zeroed by the init kernel and
+// written by one block of a launch at a time (the last to arrive, when the others
+// have read what they need); every sweep kernel reads `done` first and returns at
+// once when the solve is over, so that unrolled iteration sequences stop doing
+// work after convergence.
 struct SolveState {
     // parameters (init kernel)
     double tol;
@@ -37,7 +40,8 @@ struct SolveState {
     int max_iter;
     int max_outer;
     int precision;
-    int pad0;
+    unsigned arrive;    // groups of the running launch's blocks that have all arrived
+                        // (last_block); 0 between launches
     // setup results
     double b_mean;
     double b_sumsq;     // sum b^2 (for the FP32 scale only)
@@ -68,10 +72,10 @@ struct SolveState {
     int p1_work;        // launches of the residual sweep P1 that did their work
     int since_best;
     int stop_next;      // the inner phase ends after the update of the iteration in progress:
-                        // the next inner residual sweep idles and its decision closes the phase
+                        // the next inner residual sweep evaluates nothing and closes the phase
     int upd_due;        // the last inner evaluation went on with the phase and its update (the
                         // y, z, y and x sweeps) has not run yet: the next inner residual sweep
-                        // and its decision idle until it has (the x sweep clears it)
+                        // idles until it has (the x sweep clears it)
     int checked;        // the last outer residual was a check (sums alone) that did not end the
                         // solve: `rel` is the residual of the current p, no update is pending
     double inv_s;       // r32 = r * inv_s (a power of two)
@@ -128,8 +132,6 @@ hipError_t launch_init(const GridArgs& g, const Slot* slots, int nslots, double 
                        int max_outer, int precision, hipStream_t s);
 hipError_t launch_setup(const GridArgs& g, const Geometry& geo, const Slot* slots, int nslots,
                         bool write_rho32, hipStream_t s);
-hipError_t launch_setup_finalize(const GridArgs& g, const Geometry& geo, const Slot* slots, int nslots,
-                                 hipStream_t s);
 // One iteration of the paper's method on all slots (FP64 fields) or one inner
 // iteration (FP32 fields).
 // HIP events around the launches of one sweep kind inside solves (sweep 0: off);
@@ -155,22 +157,24 @@ hipError_t launch_inner_update(const GridArgs& g, const Geometry& geo, const Tab
 hipError_t launch_sweep(const GridArgs& g, const Tables& t, const Slot* slots, int nslots, bool fp32, int which,
                         hipStream_t s);
 // poisson_sweeps.hip: one sweep; mode 0 iteration, mode 1 the stand-alone L^+ q
-// sweep (FP64).  *nunits (may be NULL) receives the number of partial sums P1
-// wrote.  `share`: fraction of the resident blocks the persistent sweeps take.
+// sweep (FP64).  `share`: fraction of the resident blocks the persistent sweeps
+// take.  decide: P1 ends in the iteration's decision (false: timing, the state
+// stays as it is).
 hipError_t launch_sweep_mode(const GridArgs& g, const Tables& t, const Slot* slots, int nslots, bool fp32, int which,
-                             int mode, hipStream_t s, int* nunits, float share = 1.0f, int stage = 1);
+                             int mode, hipStream_t s, float share = 1.0f, int stage = 1, bool decide = true);
 unsigned sweep_groups_x(const GridArgs& g);
 // FP32_REFINE: whether rows of this length take the outer residual fused with
 // the first inner sweep's residual (one marching column per thread), and that
-// sweep alone (no decision); *nunits receives the number of partial sums.
+// sweep alone, ending in its decision unless `decide` is false.
 // write = false: the partial sums alone (no r32, no transformed residual).
 bool outer_fusable(const GridArgs& g);
 hipError_t launch_outer_fused(const GridArgs& g, const Tables& t, const Slot* slots, int nslots, hipStream_t s,
-                              int* nunits, float share = 1.0f, bool write = true);
+                              float share = 1.0f, bool write = true, bool decide = true);
 // FP32_REFINE outer step pieces.
-// the FP64 outer residual sweep alone (no decision); *nunits (may be NULL)
-// receives the number of partial sums it wrote
-hipError_t launch_outer_resid_sweep(const GridArgs& g, const Slot* slots, int nslots, hipStream_t s, int* nunits);
+// the FP64 outer residual sweep of rows shorter than 16, not fused, ending in its
+// decision unless `decide` is false
+hipError_t launch_outer_resid_sweep(const GridArgs& g, const Slot* slots, int nslots, hipStream_t s,
+                                    bool decide = true);
 // The FP64 outer residual of a refinement step and its decision; where the
 // rows allow (*fused), fused with the first inner sweep's residual and, with
 // `tail`, followed by the rest of that sweep.  Without `tail` (the final check

@@ -39,6 +39,7 @@ __global__ void __launch_bounds__(256) k_init(const Slot* __restrict__ slots, do
     unsigned long long* w = reinterpret_cast<unsigned long long*>(st);
     constexpr int words = (int)(sizeof(SolveState) / sizeof(unsigned long long));
     for (int q = threadIdx.x; q < words; q += 256) w[q] = 0ull;
+    if (threadIdx.x < kArriveGroups) *arrive_group(slots[blockIdx.x].partial, threadIdx.x) = 0u;
     __syncthreads();
     if (threadIdx.x != 0) return;
     st->tol = slots[blockIdx.x].tol;
@@ -49,6 +50,55 @@ __global__ void __launch_bounds__(256) k_init(const Slot* __restrict__ slots, do
     st->precision = precision;
     st->status = POISSON_OK;
     st->inv_s = 1.0;
+}
+
+__device__ double pow2_near(double x) {
+    // nearest power of two to x (x > 0, finite), else 1
+    if (!(x > 0.0) || !isfinite(x)) return 1.0;
+    return ldexp(1.0, (int)lrint(log2(x)));
+}
+
+// The blocks' results of k_setup, taken together by its last block.
+__device__ void setup_finalize(const GridArgs& g, const Slot& s, double* red) {
+    SolveState* st = s.st;
+    double sb = 0.0, sb2 = 0.0, mn = INFINITY, mx = -INFINITY, bad = 0.0;
+#pragma unroll 4
+    for (unsigned b = threadIdx.x; b < gridDim.x; b += kPtThreads) {
+        const double* in = s.partial + (unsigned long long)b * 8;
+        sb += get_shared(in + 0);
+        sb2 += get_shared(in + 1);
+        mn = fmin(mn, get_shared(in + 2));
+        mx = fmax(mx, get_shared(in + 3));
+        bad += get_shared(in + 4);
+    }
+    const int w = threadIdx.x / 64, lane = threadIdx.x % 64;
+    sb = wave_sum(sb); sb2 = wave_sum(sb2); bad = wave_sum(bad);
+    mn = wave_min(mn); mx = wave_max(mx);
+    if (lane == 0) {
+        red[w * 5 + 0] = sb; red[w * 5 + 1] = sb2; red[w * 5 + 2] = mn; red[w * 5 + 3] = mx;
+        red[w * 5 + 4] = bad;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int u = 1; u < kPtThreads / 64; ++u) {
+            sb += red[u * 5 + 0]; sb2 += red[u * 5 + 1]; mn = fmin(mn, red[u * 5 + 2]);
+            mx = fmax(mx, red[u * 5 + 3]); bad += red[u * 5 + 4];
+        }
+        st->b_mean = sb / (double)g.n;
+        st->b_sumsq = sb2;
+        st->rho_min = mn;
+        st->rho_max = mx;
+        st->bad = bad > 0.0;
+        // scale of the first FP32 right-hand side: near the RMS of b
+        st->inv_s = 1.0 / pow2_near(sqrt(sb2 / (double)g.n));
+        // density ratio the scaled batched reciprocals of the sweeps support
+        const double max_ratio = (st->precision == POISSON_FP32_REFINE) ? 1e8 : 1e20;
+        if (!(mx <= max_ratio * mn)) bad += 1.0;
+        if (bad > 0.0) {
+            st->done = 1;
+            st->status = POISSON_EDOMAIN;
+        }
+    }
 }
 
 // rho: min, max, validity; b: sum, sum of squares, validity; optional FP32 copy of rho.
@@ -95,93 +145,13 @@ k_setup(GridArgs g, const Slot* __restrict__ slots, int write_rho32) {
             mx = fmax(mx, red[u * 5 + 3]); bad += red[u * 5 + 4];
         }
         double* out = s.partial + (long long)blockIdx.x * 8;
-        out[0] = sb; out[1] = sb2; out[2] = mn; out[3] = mx; out[4] = bad;
+        put_shared(out + 0, sb);
+        put_shared(out + 1, sb2);
+        put_shared(out + 2, mn);
+        put_shared(out + 3, mx);
+        put_shared(out + 4, bad);
     }
-}
-
-__device__ double pow2_near(double x) {
-    // nearest power of two to x (x > 0, finite), else 1
-    if (!(x > 0.0) || !isfinite(x)) return 1.0;
-    return ldexp(1.0, (int)lrint(log2(x)));
-}
-
-__global__ void __launch_bounds__(256) k_setup_finalize(GridArgs g, const Slot* __restrict__ slots, int nblk) {
-    __shared__ double red[4 * 5];
-    const Slot& s = slots[blockIdx.x];
-    SolveState* st = s.st;
-    double sb = 0.0, sb2 = 0.0, mn = INFINITY, mx = -INFINITY, bad = 0.0;
-    for (int b = threadIdx.x; b < nblk; b += 256) {
-        const double* in = s.partial + (long long)b * 8;
-        sb += in[0]; sb2 += in[1]; mn = fmin(mn, in[2]); mx = fmax(mx, in[3]); bad += in[4];
-    }
-    const int w = threadIdx.x / 64, lane = threadIdx.x % 64;
-    sb = wave_sum(sb); sb2 = wave_sum(sb2); bad = wave_sum(bad);
-    mn = wave_min(mn); mx = wave_max(mx);
-    if (lane == 0) {
-        red[w * 5 + 0] = sb; red[w * 5 + 1] = sb2; red[w * 5 + 2] = mn; red[w * 5 + 3] = mx;
-        red[w * 5 + 4] = bad;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int u = 1; u < 4; ++u) {
-            sb += red[u * 5 + 0]; sb2 += red[u * 5 + 1]; mn = fmin(mn, red[u * 5 + 2]);
-            mx = fmax(mx, red[u * 5 + 3]); bad += red[u * 5 + 4];
-        }
-        st->b_mean = sb / (double)g.n;
-        st->b_sumsq = sb2;
-        st->rho_min = mn;
-        st->rho_max = mx;
-        st->bad = bad > 0.0;
-        // scale of the first FP32 right-hand side: near the RMS of b
-        st->inv_s = 1.0 / pow2_near(sqrt(sb2 / (double)g.n));
-        // density ratio the scaled batched reciprocals of the sweeps support
-        const double max_ratio = (st->precision == POISSON_FP32_REFINE) ? 1e8 : 1e20;
-        if (!(mx <= max_ratio * mn)) bad += 1.0;
-        if (bad > 0.0) {
-            st->done = 1;
-            st->status = POISSON_EDOMAIN;
-        }
-    }
-}
-
-// ---- decisions (one block per solve, after the sweep that wrote the sums) -------------
-
-// One block of kDecideThreads per solve: the units' sums of a residual sweep
-// (up to one per row pair) are read by many threads at once.
-constexpr int kDecideThreads = 1024;
-
-// After P1 of an iteration: FP64 path (fp32 = 0) or an FP32 inner sweep.
-__global__ void __launch_bounds__(kDecideThreads) k_decide_iter(GridArgs g, const Slot* __restrict__ slots,
-                                                                int nunits, int fp32) {
-    __shared__ double red[(kDecideThreads / 64) * 4];
-    const Slot& s = slots[blockIdx.x];
-    SolveState* st = s.st;
-    if (fp32 ? (st->done || st->stage != 1 || st->inner_done || st->upd_due) : st->done) return;
-    double sums[4] = {0.0, 0.0, 0.0, 0.0};
-    if (!(fp32 && st->stop_next)) sum_units<kDecideThreads, 4>(s.partial, (unsigned)nunits, sums, red);
-    if (threadIdx.x != 0) return;
-    if (fp32) decide_inner(st, sums, kMaxInnerPerStep);
-    else decide_fp64(g, st, sums);
-}
-
-// After the FP64 outer residual of a refinement step.  mode 0: the residual
-// alone (r32 written), 1: fused with the first inner sweep's residual, 2: its
-// sums alone (a check: no step starts from it).
-__global__ void __launch_bounds__(kDecideThreads) k_decide_outer(GridArgs g, const Slot* __restrict__ slots,
-                                                                 int nunits, int mode) {
-    __shared__ double red[(kDecideThreads / 64) * 5];
-    const Slot& s = slots[blockIdx.x];
-    SolveState* st = s.st;
-    if (st->done || st->stage != 0) return;
-    double sums[5];
-    sum_units<kDecideThreads, 5>(s.partial, (unsigned)nunits, sums, red);
-    if (threadIdx.x == 0) decide_outer(g, st, sums, mode == 1, mode == 2);
-}
-
-// After the rest of a fused first inner sweep: the inner sweeps go on.
-__global__ void __launch_bounds__(64) k_tail_done(const Slot* __restrict__ slots) {
-    SolveState* st = slots[blockIdx.x].st;
-    if (threadIdx.x == 0 && !st->done && st->stage == kStageTail) st->stage = 1;
+    if (last_block(s)) setup_finalize(g, s, red);
 }
 
 // ---- pointwise FP64 stencil sweeps -------------------------------------------------
@@ -240,7 +210,8 @@ k_stencil(GridArgs g, const Slot* __restrict__ slots, const double* __restrict__
 constexpr int kOuterElems = 2048;  // (pair, column) elements per block
 
 template <int N, int COEF, int WEIGHT>
-__global__ void __launch_bounds__(kPtThreads) k_outer_resid_rows(GridArgs g, const Slot* __restrict__ slots) {
+__global__ void __launch_bounds__(kPtThreads)
+k_outer_resid_rows(GridArgs g, const Slot* __restrict__ slots, int decide) {
     constexpr int RPB = N >= kOuterElems ? 1 : kOuterElems / N;  // row pairs per block
     __shared__ double red[(kPtThreads / 64) * 5];
     __shared__ int s_j0[RPB], s_k0[RPB];
@@ -304,6 +275,9 @@ __global__ void __launch_bounds__(kPtThreads) k_outer_resid_rows(GridArgs g, con
         if (it + 1 < IT) evaluate(it + 1, B);
     }
     put_unit_sums<kPtThreads, 5>(acc, red, s.partial + (unsigned long long)blockIdx.x * kPartialStride);
+    if (!decide || !last_block(s)) return;
+    sum_units<kPtThreads, 5>(s.partial, gridDim.x, acc, red);
+    if (threadIdx.x == 0) decide_outer(g, st, acc, false);
 }
 
 template <int N>
@@ -313,10 +287,11 @@ static int blocks_outer(const GridArgs& g) {
     return (int)((np + RPB - 1) / RPB);
 }
 
-// FP32_REFINE outer update: p += d32 / inv_s - p_shift (FP64), then the next scale.
+// FP32_REFINE outer update: p += d32 / inv_s - p_shift (FP64); the last block opens
+// the next outer residual with its scale.
 __global__ void __launch_bounds__(kPtThreads) k_outer_update(GridArgs g, const Slot* __restrict__ slots) {
     const Slot& s = slots[blockIdx.y];
-    const SolveState* st = s.st;
+    SolveState* st = s.st;
     if (st->done || st->stage != 2) return;
     const double scale = 1.0 / st->inv_s;
     // mean of the current p (FP64 sum of the outer residual sweep): removing it
@@ -325,12 +300,7 @@ __global__ void __launch_bounds__(kPtThreads) k_outer_update(GridArgs g, const S
     const unsigned n = (unsigned)g.n, stride = gridDim.x * kPtThreads;
     for (unsigned c = blockIdx.x * kPtThreads + threadIdx.x; c < n; c += stride)
         gptr(s.p)[c] = gptr(s.p)[c] + (double)gptr(s.d32)[c] * scale - shift;
-}
-
-// One block per slot: between the outer update and the next outer residual.
-__global__ void __launch_bounds__(64) k_outer_advance(GridArgs g, const Slot* __restrict__ slots) {
-    SolveState* st = slots[blockIdx.x].st;
-    if (st->done || st->stage != 2 || threadIdx.x != 0) return;
+    if (!last_block(s) || threadIdx.x != 0) return;
     st->stage = 0;
     // predicted size of the next FP64 residual: ||r|| times the inner reduction
     const double est = st->r_norm * fmax(st->rel_in, 1e-30);
@@ -395,6 +365,7 @@ Geometry make_geometry(const GridArgs& g) {
     const int row_pairs = (int)((long long)g.ny * g.nz / 2);
     geo.max_blocks = std::max(std::max(std::max(std::max(geo.blocks_x, geo.blocks_pt), nbo), kMaxSetupBlocks),
                               row_pairs);
+    static_assert(kArriveGroups * kArriveStep <= kMaxSetupBlocks, "the arrival counters lie in the sets");
     geo.share = 1.0f;
     return geo;
 }
@@ -409,16 +380,8 @@ hipError_t launch_init(const GridArgs& g, const Slot* slots, int nslots, double 
 hipError_t launch_setup(const GridArgs& g, const Geometry& geo, const Slot* slots, int nslots, bool write_rho32,
                         hipStream_t s) {
     (void)geo;
-    const int nb = std::min(pt_blocks(g), kMaxSetupBlocks);
+    const int nb = std::min(pt_blocks(g), 2048);
     k_setup<<<dim3(nb, nslots), kPtThreads, 0, s>>>(g, slots, write_rho32 ? 1 : 0);
-    return hipGetLastError();
-}
-
-hipError_t launch_setup_finalize(const GridArgs& g, const Geometry& geo, const Slot* slots, int nslots,
-                                 hipStream_t s) {
-    (void)geo;
-    const int nb = std::min(pt_blocks(g), kMaxSetupBlocks);
-    k_setup_finalize<<<nslots, 256, 0, s>>>(g, slots, nb);
     return hipGetLastError();
 }
 
@@ -429,27 +392,18 @@ hipError_t launch_setup_finalize(const GridArgs& g, const Geometry& geo, const S
 static hipError_t five_sweeps(const GridArgs& g, const Tables& t, const Slot* slots, int nslots, bool fp32,
                               int mode, hipStream_t s, SweepTimer* tm, float share = 1.0f, int parts = 3) {
     hipError_t e;
-    int nunits = 0;
     // one sweep, bracketed by the timer's events when it times this sweep
     auto sweep = [&](int which) -> hipError_t {
         const bool timed = tm && tm->sweep == which && tm->fp32 == fp32 && tm->used < SweepTimer::kCap;
         if (timed && (e = hipEventRecord(tm->ev[2 * tm->used], s)) != hipSuccess) return e;
-        if ((e = launch_sweep_mode(g, t, slots, nslots, fp32, which, mode, s, which == 1 ? &nunits : nullptr,
-                                   share)) != hipSuccess)
-            return e;
+        if ((e = launch_sweep_mode(g, t, slots, nslots, fp32, which, mode, s, share)) != hipSuccess) return e;
         if (timed) {
             if ((e = hipEventRecord(tm->ev[2 * tm->used + 1], s)) != hipSuccess) return e;
             ++tm->used;
         }
         return hipSuccess;
     };
-    if (parts & 1) {
-        if ((e = sweep(1)) != hipSuccess) return e;
-        if (mode == 0) {
-            k_decide_iter<<<nslots, kDecideThreads, 0, s>>>(g, slots, nunits, fp32 ? 1 : 0);
-            if ((e = hipGetLastError()) != hipSuccess) return e;
-        }
-    }
+    if ((parts & 1) && (e = sweep(1)) != hipSuccess) return e;
     if (!(parts & 2)) return hipSuccess;
     if ((e = sweep(2)) != hipSuccess) return e;
     if ((e = sweep(3)) != hipSuccess) return e;
@@ -459,7 +413,7 @@ static hipError_t five_sweeps(const GridArgs& g, const Tables& t, const Slot* sl
 
 hipError_t launch_sweep(const GridArgs& g, const Tables& t, const Slot* slots, int nslots, bool fp32, int which,
                         hipStream_t s) {
-    return launch_sweep_mode(g, t, slots, nslots, fp32, which, 0, s, nullptr);
+    return launch_sweep_mode(g, t, slots, nslots, fp32, which, 0, s, 1.0f, 1, false);
 }
 
 hipError_t launch_iteration(const GridArgs& g, const Geometry& geo, const Tables& t, const Slot* slots,
@@ -477,13 +431,12 @@ hipError_t launch_inner_update(const GridArgs& g, const Geometry& geo, const Tab
     return five_sweeps(g, t, slots, nslots, true, 0, s, tm, geo.share, 2);
 }
 
-hipError_t launch_outer_resid_sweep(const GridArgs& g, const Slot* slots, int nslots, hipStream_t s, int* nunits) {
+hipError_t launch_outer_resid_sweep(const GridArgs& g, const Slot* slots, int nslots, hipStream_t s, bool decide) {
     return dispatch_len(g.nx, [&]<int N>() {
         const int nb = blocks_outer<N>(g);
-        if (nunits) *nunits = nb;
         return dispatch_op(g.coef, g.weight, [&]<int C, int W>() {
             if constexpr (N < 16) {
-                k_outer_resid_rows<N, C, W><<<dim3(nb, nslots), kPtThreads, 0, s>>>(g, slots);
+                k_outer_resid_rows<N, C, W><<<dim3(nb, nslots), kPtThreads, 0, s>>>(g, slots, decide ? 1 : 0);
                 return hipGetLastError();
             } else {
                 return hipErrorInvalidValue;
@@ -496,37 +449,26 @@ hipError_t launch_outer_tail(const GridArgs& g, const Geometry& geo, const Table
                              int nslots, hipStream_t s) {
     hipError_t e;
     for (int which : {2, 3, 2, 5})
-        if ((e = launch_sweep_mode(g, t, slots, nslots, true, which, 0, s, nullptr, geo.share, kStageTail)) !=
-            hipSuccess)
+        if ((e = launch_sweep_mode(g, t, slots, nslots, true, which, 0, s, geo.share, kStageTail)) != hipSuccess)
             return e;
-    k_tail_done<<<nslots, 64, 0, s>>>(slots);
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 hipError_t launch_outer_residual(const GridArgs& g, const Geometry& geo, const Tables& t, const Slot* slots,
                                  int nslots, hipStream_t s, bool* fused, bool tail) {
-    int nu = 0;
     hipError_t e;
     const bool fu = outer_fusable(g);
     if (fused) *fused = fu;
-    if (fu) {
-        if ((e = launch_outer_fused(g, t, slots, nslots, s, &nu, geo.share, tail)) != hipSuccess) return e;
-    } else if ((e = launch_outer_resid_sweep(g, slots, nslots, s, &nu)) != hipSuccess) {
-        return e;
-    }
-    k_decide_outer<<<nslots, kDecideThreads, 0, s>>>(g, slots, nu, fu ? (tail ? 1 : 2) : 0);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    if (!fu || !tail) return hipSuccess;
+    if (!fu) return launch_outer_resid_sweep(g, slots, nslots, s);
+    if ((e = launch_outer_fused(g, t, slots, nslots, s, geo.share, tail)) != hipSuccess) return e;
+    if (!tail) return hipSuccess;
     // the rest of the first inner sweep: P2, P3, P4, P5 (which stores dp as d32)
     return launch_outer_tail(g, geo, t, slots, nslots, s);
 }
 
 hipError_t launch_outer_update(const GridArgs& g, const Geometry& geo, const Slot* slots, int nslots,
                                hipStream_t s) {
-    k_outer_update<<<dim3(geo.blocks_pt, nslots), kPtThreads, 0, s>>>(g, slots);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    k_outer_advance<<<nslots, 64, 0, s>>>(g, slots);
+    k_outer_update<<<dim3(std::min(geo.blocks_pt, 2048), nslots), kPtThreads, 0, s>>>(g, slots);
     return hipGetLastError();
 }
 

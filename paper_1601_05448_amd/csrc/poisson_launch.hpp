@@ -21,7 +21,7 @@ constexpr unsigned kWideGroups = 512;
 // FP32 fields of the slots.
 template <typename T>
 hipError_t launch_resid(const GridArgs& g, const Tables& t, const Slot* slots, int nslots, int mode, hipStream_t s,
-                        int* nunits, float share);
+                        float share, bool decide);
 template <typename T>
 hipError_t launch_cols_y(const GridArgs& g, const Tables& t, const Slot* slots, int nslots, int mode, hipStream_t s,
                          float share, int stage);

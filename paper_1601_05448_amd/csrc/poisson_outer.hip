@@ -4,11 +4,22 @@
 
 #include <algorithm>
 
+#include "poisson_control.hpp"
 #include "poisson_device.hpp"
 #include "poisson_launch.hpp"
 #include "poisson_rows.hpp"
 
 namespace pois {
+
+// The end of the sweep: the last block adds the units' sums and decides.
+template <int NT>
+__device__ __forceinline__ void outer_decide(const GridArgs& g, const Slot& s, unsigned units, int write, int decide,
+                                             double* red) {
+    if (!decide || !last_block(s)) return;
+    double sums[5];
+    sum_units<NT, 5>(s.partial, units, sums, red);
+    if (threadIdx.x == 0) decide_outer(g, s.st, sums, write != 0, write == 0);
+}
 
 // FP32_REFINE: the FP64 outer residual of a refinement step fused with the
 // residual half of its first FP32 inner sweep.  The inner correction starts at
@@ -21,7 +32,7 @@ namespace pois {
 // check of a solve, which usually ends it: no r32, no transform, no W32).
 template <int N, int COEF, int WEIGHT, int BCX>
 __global__ void __launch_bounds__((RowTile<N, true>::NT), 2)
-k_outer_resid_dhtx(GridArgs g, const Slot* __restrict__ slots, Tables tb, int write, int nflush) {
+k_outer_resid_dhtx(GridArgs g, const Slot* __restrict__ slots, Tables tb, int write, int nflush, int decide) {
     using Z = RowTile<N, true>;
     using RF = RowFlush<double, N>;
     using LF = LineFft<float, N, true, RF::SET>;
@@ -144,12 +155,13 @@ k_outer_resid_dhtx(GridArgs g, const Slot* __restrict__ slots, Tables tb, int wr
         }
         put_unit_sums<Z::NT, 5>(acc, red, s.partial + (unsigned long long)tile * kPartialStride);
     }
+    outer_decide<Z::NT>(g, s, ntiles, write, decide, red);
 }
 
 // The same on small grids, every load of a tile issued at once (see k_resid_dhtx_s).
 template <int N, int KF, int COEF, int WEIGHT>
 __global__ void __launch_bounds__((RowTile<N, false>::NT))
-k_outer_resid_dhtx_s(GridArgs g, const Slot* __restrict__ slots, Tables tb, int write) {
+k_outer_resid_dhtx_s(GridArgs g, const Slot* __restrict__ slots, Tables tb, int write, int decide) {
     using Z = RowTile<N, false>;
     using LF = LineFft<float, N, true, 1>;
     static_assert(Z::CPT == 1, "one column per thread");
@@ -238,6 +250,7 @@ k_outer_resid_dhtx_s(GridArgs g, const Slot* __restrict__ slots, Tables tb, int 
         }
         put_unit_sums<Z::NT, 5>(acc, red, s.partial + (unsigned long long)tile * kPartialStride);  // ends on a barrier
     }
+    outer_decide<Z::NT>(g, s, ntiles, write, decide, red);
 }
 
 bool outer_fusable(const GridArgs& g) { return g.nx >= 16; }
@@ -245,8 +258,8 @@ bool outer_fusable(const GridArgs& g) { return g.nx >= 16; }
 constexpr int kSmallPlanes = 2;  // of a small tile
 
 hipError_t launch_outer_fused(const GridArgs& g, const Tables& t, const Slot* slots, int nslots, hipStream_t s,
-                              int* nunits, float share, bool write) {
-    const int wr = write ? 1 : 0;
+                              float share, bool write, bool decide) {
+    const int wr = write ? 1 : 0, dec = decide ? 1 : 0;
     return dispatch_len(g.nx, [&]<int N>() {
         if constexpr (N < 16) {
             return hipErrorInvalidValue;
@@ -258,10 +271,9 @@ hipError_t launch_outer_fused(const GridArgs& g, const Tables& t, const Slot* sl
                     const unsigned nt = (((unsigned)g.ny / 2 + Z::SUB - 1) / Z::SUB) *
                                         (((unsigned)g.nz + kSmallPlanes - 1) / kSmallPlanes);
                     if (small_tiles_fit(nt, (unsigned)persistent_grid(k, Z::NT, ~0u, 1, 1.0f))) {
-                        if (nunits) *nunits = (int)nt;
                         const int nb = persistent_grid(k, Z::NT, nt, nslots, share);
                         k_outer_resid_dhtx_s<N, kSmallPlanes, CO, WE>
-                            <<<dim3(nb, nslots), Z::NT, reserve_lds(k, share), s>>>(g, slots, t, wr);
+                            <<<dim3(nb, nslots), Z::NT, reserve_lds(k, share), s>>>(g, slots, t, wr, dec);
                         return hipGetLastError();
                     }
                 }
@@ -273,10 +285,9 @@ hipError_t launch_outer_fused(const GridArgs& g, const Tables& t, const Slot* sl
                     const int nf = pick_flushes(KF, 32, strips, (unsigned)g.nz,
                                                 (unsigned)persistent_grid(k, Z::NT, ~0u, 1, 1.0f));
                     const unsigned km = (unsigned)(nf * KF), nt = strips * (((unsigned)g.nz + km - 1) / km);
-                    if (nunits) *nunits = (int)nt;
                     const int nb = persistent_grid(k, Z::NT, nt, nslots, share);
                     k_outer_resid_dhtx<N, CO, WE, BC>
-                        <<<dim3(nb, nslots), Z::NT, reserve_lds(k, share), s>>>(g, slots, t, wr, nf);
+                        <<<dim3(nb, nslots), Z::NT, reserve_lds(k, share), s>>>(g, slots, t, wr, nf, dec);
                     return hipGetLastError();
                 });
             });

@@ -6,24 +6,52 @@
 
 #include <algorithm>
 
+#include "poisson_control.hpp"
 #include "poisson_device.hpp"
 #include "poisson_launch.hpp"
 #include "poisson_rows.hpp"
 
 namespace pois {
 
+// The start of an evaluation: whether this launch of P1 has nothing to evaluate
+// for the solve.  The phase of an FP32 step that was predicted to end after the
+// update before it is closed here, by the last block (when every block has read
+// the state that sent it here).
+template <typename T>
+__device__ __forceinline__ bool p1_idle(const Slot& s, int decide) {
+    if (IterView<T>::skip_p1(s.st)) return true;
+    if constexpr (sizeof(T) == 4) {
+        if (s.st->stop_next != 0) {
+            if (decide && last_block(s) && threadIdx.x == 0) close_inner(s.st);
+            return true;
+        }
+    }
+    return false;
+}
+
+// The end of an evaluation: the last block adds the units' sums and decides.
+template <typename T, int NT>
+__device__ __forceinline__ void p1_decide(const GridArgs& g, const Slot& s, unsigned units, int decide, double* red) {
+    if (!decide || !last_block(s)) return;
+    double sums[4];
+    sum_units<NT, 4>(s.partial, units, sums, red);
+    if (threadIdx.x != 0) return;
+    if constexpr (sizeof(T) == 4) decide_inner(s.st, sums, kMaxInnerPerStep);
+    else decide_fp64(g, s.st, sums);
+}
+
 // ---- P1: residual, weight, Hartley along x --------------------------------------
 // MODE 0: stencil residual of the iteration view; MODE 1: q = b (copy, for the
 // stand-alone L^+ sweep).
 template <typename T, int N, int MODE, int COEF, int WEIGHT>
 __global__ void __launch_bounds__((LineCfg<T, N>::NT))
-k_resid_dhtx(GridArgs g, const Slot* __restrict__ slots, Tables tb) {
+k_resid_dhtx(GridArgs g, const Slot* __restrict__ slots, Tables tb, int decide) {
     using C = LineCfg<T, N>;
     __shared__ cpx<T> lds[C::L * C::LS];
     __shared__ cpx<T> tw[N];
     __shared__ double red[(C::NT / 64) * 4];
     const Slot& s = slots[blockIdx.y];
-    if (MODE == 0 && IterView<T>::skip_p1(s.st)) return;
+    if (MODE == 0 && p1_idle<T>(s, decide)) return;
     const cpx<T>* twg = twiddles<T>(tb, 0);
     const cpx<T>* twc = dct_twiddles<T>(tb);
     for (int e = threadIdx.x; e < N; e += C::NT) tw[e] = twg[e];
@@ -108,6 +136,7 @@ k_resid_dhtx(GridArgs g, const Slot* __restrict__ slots, Tables tb) {
         if (grp >= ngroups) break;
         __syncthreads();  // the next group overwrites the lines
     }
+    if (MODE == 0) p1_decide<T, C::NT>(g, s, ngroups, decide, red);
 }
 
 // P1 on rows of 16 and more: the residual of a tile of `nflush` KF planes x
@@ -129,7 +158,7 @@ constexpr int resid_min_waves() {
 
 template <typename T, int N, int COEF, int WEIGHT, int BCX>
 __global__ void __launch_bounds__((RowTile<N, true>::NT), (resid_min_waves<T, N>()))
-k_resid_dhtx_z(GridArgs g, const Slot* __restrict__ slots, Tables tb, int nflush) {
+k_resid_dhtx_z(GridArgs g, const Slot* __restrict__ slots, Tables tb, int nflush, int decide) {
     using Z = RowTile<N, true>;
     using RF = RowFlush<T, N>;
     using LF = LineFft<T, N, true, RF::SET>;
@@ -139,7 +168,7 @@ k_resid_dhtx_z(GridArgs g, const Slot* __restrict__ slots, Tables tb, int nflush
     __shared__ double red[(Z::NT / 64) * 4];
     __shared__ PlaneRows<T> xb[2 * Z::SUB * Z::XV];  // x neighbours, double-buffered by step parity
     const Slot& s = slots[blockIdx.y];
-    if (IterView<T>::skip_p1(s.st)) return;
+    if (p1_idle<T>(s, decide)) return;
     const cpx<T>* twg = twiddles<T>(tb, 0);
     const cpx<T>* twc = dct_twiddles<T>(tb);
     for (int e = threadIdx.x; e < N; e += Z::NT) tw[e] = twg[e];
@@ -264,6 +293,7 @@ k_resid_dhtx_z(GridArgs g, const Slot* __restrict__ slots, Tables tb, int nflush
         }
         put_unit_sums<Z::NT, 4>(acc, red, s.partial + (unsigned long long)tile * kPartialStride);
     }
+    p1_decide<T, Z::NT>(g, s, ntiles, decide, red);
 }
 
 // P1 on small grids, rows of 16 to 512: a tile of KF planes x SUB row pairs whose
@@ -272,7 +302,7 @@ k_resid_dhtx_z(GridArgs g, const Slot* __restrict__ slots, Tables tb, int nflush
 // its time on one load latency per plane in a few blocks.
 template <typename T, int N, int KF, int COEF, int WEIGHT>
 __global__ void __launch_bounds__((RowTile<N, false>::NT))
-k_resid_dhtx_s(GridArgs g, const Slot* __restrict__ slots, Tables tb) {
+k_resid_dhtx_s(GridArgs g, const Slot* __restrict__ slots, Tables tb, int decide) {
     using Z = RowTile<N, false>;
     using LF = LineFft<T, N, true, 1>;
     static_assert(Z::CPT == 1, "one column per thread");
@@ -281,7 +311,7 @@ k_resid_dhtx_s(GridArgs g, const Slot* __restrict__ slots, Tables tb) {
     __shared__ double red[(Z::NT / 64) * 4];
     __shared__ PlaneRows<T> xb[KF * Z::SUB * Z::XV];
     const Slot& s = slots[blockIdx.y];
-    if (IterView<T>::skip_p1(s.st)) return;
+    if (p1_idle<T>(s, decide)) return;
     const cpx<T>* twg = twiddles<T>(tb, 0);
     const cpx<T>* twc = dct_twiddles<T>(tb);
     for (int e = threadIdx.x; e < N; e += Z::NT) tw[e] = twg[e];
@@ -358,18 +388,18 @@ k_resid_dhtx_s(GridArgs g, const Slot* __restrict__ slots, Tables tb) {
         });
         put_unit_sums<Z::NT, 4>(acc, red, s.partial + (unsigned long long)tile * kPartialStride);  // ends on a barrier
     }
+    p1_decide<T, Z::NT>(g, s, ntiles, decide, red);
 }
 
 // Gathered rows: `mode` 1 (any length), or rows shorter than 16.
 template <typename T, int N, int MODE, int CO, int WE>
 static hipError_t run_gather(const GridArgs& g, const Tables& t, const Slot* slots, int nslots, hipStream_t s,
-                             int* nunits, float share) {
+                             float share, int decide) {
     using C = LineCfg<T, N>;
     const unsigned ng = ((unsigned)(g.ny * g.nz / 2) + C::L - 1) / C::L;
     const void* k = (const void*)&k_resid_dhtx<T, N, MODE, CO, WE>;
     const int nb = persistent_grid(k, C::NT, ng, nslots, share);
-    if (nunits) *nunits = (int)ng;
-    k_resid_dhtx<T, N, MODE, CO, WE><<<dim3(nb, nslots), C::NT, reserve_lds(k, share), s>>>(g, slots, t);
+    k_resid_dhtx<T, N, MODE, CO, WE><<<dim3(nb, nslots), C::NT, reserve_lds(k, share), s>>>(g, slots, t, decide);
     return hipGetLastError();
 }
 
@@ -378,22 +408,21 @@ constexpr int kSmallPlanes = 2;
 
 template <typename T, int N, int CO, int WE>
 static hipError_t run_small(const GridArgs& g, const Tables& t, const Slot* slots, int nslots, hipStream_t s,
-                            int* nunits, float share, bool* fits) {
+                            float share, int decide, bool* fits) {
     using Z = RowTile<N, false>;
     const void* k = (const void*)&k_resid_dhtx_s<T, N, kSmallPlanes, CO, WE>;
     const unsigned nt =
         (((unsigned)g.ny / 2 + Z::SUB - 1) / Z::SUB) * (((unsigned)g.nz + kSmallPlanes - 1) / kSmallPlanes);
     *fits = small_tiles_fit(nt, (unsigned)persistent_grid(k, Z::NT, ~0u, 1, 1.0f));
     if (!*fits) return hipSuccess;
-    if (nunits) *nunits = (int)nt;
     const int nb = persistent_grid(k, Z::NT, nt, nslots, share);
-    k_resid_dhtx_s<T, N, kSmallPlanes, CO, WE><<<dim3(nb, nslots), Z::NT, reserve_lds(k, share), s>>>(g, slots, t);
+    k_resid_dhtx_s<T, N, kSmallPlanes, CO, WE><<<dim3(nb, nslots), Z::NT, reserve_lds(k, share), s>>>(g, slots, t, decide);
     return hipGetLastError();
 }
 
 template <typename T, int N, int CO, int WE, int BC>
 static hipError_t run_march(const GridArgs& g, const Tables& t, const Slot* slots, int nslots, hipStream_t s,
-                            int* nunits, float share) {
+                            float share, int decide) {
     using Z = RowTile<N, true>;
     constexpr int KF = RowFlush<T, N>::KF;
     const void* k = (const void*)&k_resid_dhtx_z<T, N, CO, WE, BC>;
@@ -404,9 +433,8 @@ static hipError_t run_march(const GridArgs& g, const Tables& t, const Slot* slot
     const int most = sizeof(T) == 4 && N >= 512 && strips >= 256 ? 16 : 32;
     const int nf = pick_flushes(KF, most, strips, (unsigned)g.nz, (unsigned)persistent_grid(k, Z::NT, ~0u, 1, 1.0f));
     const unsigned km = (unsigned)(nf * KF), nt = strips * (((unsigned)g.nz + km - 1) / km);
-    if (nunits) *nunits = (int)nt;
     const int nb = persistent_grid(k, Z::NT, nt, nslots, share);
-    k_resid_dhtx_z<T, N, CO, WE, BC><<<dim3(nb, nslots), Z::NT, reserve_lds(k, share), s>>>(g, slots, t, nf);
+    k_resid_dhtx_z<T, N, CO, WE, BC><<<dim3(nb, nslots), Z::NT, reserve_lds(k, share), s>>>(g, slots, t, nf, decide);
     return hipGetLastError();
 }
 
@@ -414,20 +442,21 @@ static hipError_t run_march(const GridArgs& g, const Tables& t, const Slot* slot
 // sums are the same bits in every batch and share.
 template <typename T>
 hipError_t launch_resid(const GridArgs& g, const Tables& t, const Slot* slots, int nslots, int mode, hipStream_t s,
-                        int* nunits, float share) {
+                        float share, bool dec) {
+    const int decide = dec ? 1 : 0;
     return dispatch_len(g.nx, [&]<int N>() {
-        if (mode == 1) return run_gather<T, N, 1, 0, 0>(g, t, slots, nslots, s, nunits, share);
+        if (mode == 1) return run_gather<T, N, 1, 0, 0>(g, t, slots, nslots, s, share, decide);
         return dispatch_op(g.coef, g.weight, [&]<int CO, int WE>() {
             if constexpr (N < 16) {
-                return run_gather<T, N, 0, CO, WE>(g, t, slots, nslots, s, nunits, share);
+                return run_gather<T, N, 0, CO, WE>(g, t, slots, nslots, s, share, decide);
             } else {
                 if constexpr (N <= 512) {
                     bool fits = false;
-                    const hipError_t e = run_small<T, N, CO, WE>(g, t, slots, nslots, s, nunits, share, &fits);
+                    const hipError_t e = run_small<T, N, CO, WE>(g, t, slots, nslots, s, share, decide, &fits);
                     if (fits) return e;
                 }
                 return dispatch_bc(g.bcx, [&]<int BC>() {
-                    return run_march<T, N, CO, WE, BC>(g, t, slots, nslots, s, nunits, share);
+                    return run_march<T, N, CO, WE, BC>(g, t, slots, nslots, s, share, decide);
                 });
             }
         });

@@ -3,6 +3,6 @@
 
 namespace pois {
 
-template hipError_t launch_resid<float>(const GridArgs&, const Tables&, const Slot*, int, int, hipStream_t, int*, float);
+template hipError_t launch_resid<float>(const GridArgs&, const Tables&, const Slot*, int, int, hipStream_t, float, bool);
 
 }  // namespace pois

@@ -235,8 +235,6 @@ static int launch_class(poisson_server_s* s, SizeClass* c) {
                              c->stream)) != hipSuccess)
             return hip_status(e);
         if ((e = launch_setup(c->g, c->geo, c->d_slots, nfresh, fp32, c->stream)) != hipSuccess) return hip_status(e);
-        if ((e = launch_setup_finalize(c->g, c->geo, c->d_slots, nfresh, c->stream)) != hipSuccess)
-            return hip_status(e);
         for (Resident& r : c->active) r.fresh = false;
     }
     // FP64: `chunk` iterations.  FP32: one fixed sequence for solves at any

@@ -139,9 +139,9 @@ int persistent_grid(const void* kernel, int threads, unsigned ngroups, int nslot
 
 template <typename T>
 static hipError_t sweep_t(const GridArgs& g, const Tables& t, const Slot* slots, int nslots, int which, int mode,
-                          hipStream_t s, int* nunits, float share, int stage) {
+                          hipStream_t s, float share, int stage, bool decide) {
     switch (which) {
-        case 1: return launch_resid<T>(g, t, slots, nslots, mode, s, nunits, share);
+        case 1: return launch_resid<T>(g, t, slots, nslots, mode, s, share, decide);
         case 2: return launch_cols_y<T>(g, t, slots, nslots, mode, s, share, stage);
         case 3: return launch_z_solve<T>(g, t, slots, nslots, mode, s, share, stage);
         case 5: return launch_update<T>(g, t, slots, nslots, mode, s, share, stage);
@@ -150,10 +150,10 @@ static hipError_t sweep_t(const GridArgs& g, const Tables& t, const Slot* slots,
 }
 
 hipError_t launch_sweep_mode(const GridArgs& g, const Tables& t, const Slot* slots, int nslots, bool fp32, int which,
-                             int mode, hipStream_t s, int* nunits, float share, int stage) {
+                             int mode, hipStream_t s, float share, int stage, bool decide) {
     if (mode == 1) stage = 1;
-    return fp32 ? sweep_t<float>(g, t, slots, nslots, which, mode, s, nunits, share, stage)
-                : sweep_t<double>(g, t, slots, nslots, which, mode, s, nunits, share, 1);
+    return fp32 ? sweep_t<float>(g, t, slots, nslots, which, mode, s, share, stage, decide)
+                : sweep_t<double>(g, t, slots, nslots, which, mode, s, share, 1, decide);
 }
 
 unsigned sweep_groups_x(const GridArgs& g) {

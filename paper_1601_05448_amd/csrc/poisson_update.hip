@@ -148,6 +148,9 @@ k_dhtx_update(GridArgs g, const Slot* __restrict__ slots, Tables tb, int stage, 
         if (grp >= ngroups) break;
         __syncthreads();
     }
+    // the rest of a fused first inner sweep ends here: the inner sweeps go on
+    if constexpr (sizeof(T) == 4)
+        if (mode == 2 && last_block(s) && threadIdx.x == 0) s.st->stage = 1;
 }
 
 template <typename T>
