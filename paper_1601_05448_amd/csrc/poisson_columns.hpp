@@ -72,9 +72,8 @@ k_dht_cols(GridArgs g, const Slot* __restrict__ slots, Tables tb, int stage, int
     __shared__ cpx<T> lds[L * F::LS];
     __shared__ cpx<T> tw[N];
     const Slot& s = slots[blockIdx.y];
-    if (mode == 0 && IterView<T>::skip(s.st, stage)) return;
-    const cpx<T>* twg = twiddles<T>(tb, 1);
-    for (int e = threadIdx.x; e < N; e += NT) tw[e] = twg[e];
+    TwiddleLoad<T, N, NT> twl;
+    twl.load(twiddles<T>(tb, 1));
     POIS_GLOBAL T* Wc = mode == 0 ? IterView<T>(s).W : (POIS_GLOBAL T*)gptr(s.W);  // complex-indexed
     const unsigned nlines = (unsigned)(g.nxh * g.nz), ngroups = (nlines + L - 1) / L;
     const unsigned se = (unsigned)g.nxh;
@@ -93,6 +92,9 @@ k_dht_cols(GridArgs g, const Slot* __restrict__ slots, Tables tb, int stage, int
     unsigned grp = ColShape<T, N, L>::first_group(blockIdx.x, gridDim.x), base;
     bool valid;
     load(grp, valid, base);
+    loads_issued();
+    if (mode == 0 && IterView<T>::skip(s.st, stage)) return;
+    twl.store(tw);
     __syncthreads();  // twiddles
     while (true) {
         cpx<T> v[F::E];
@@ -128,9 +130,8 @@ k_dht_cols_regs(GridArgs g, const Slot* __restrict__ slots, Tables tb, int stage
     __shared__ cpx<T> lds[C::L * C::LS];
     __shared__ cpx<T> tw[N];
     const Slot& s = slots[blockIdx.y];
-    if (mode == 0 && IterView<T>::skip(s.st, stage)) return;
-    const cpx<T>* twg = twiddles<T>(tb, 1);
-    for (int e = threadIdx.x; e < N; e += C::NT) tw[e] = twg[e];
+    TwiddleLoad<T, N, C::NT> twl;
+    twl.load(twiddles<T>(tb, 1));
     POIS_GLOBAL T* Wc = mode == 0 ? IterView<T>(s).W : (POIS_GLOBAL T*)gptr(s.W);  // complex-indexed
     const unsigned nlines = (unsigned)(g.nxh * g.nz);
     const unsigned ngroups = (nlines + C::L - 1) / C::L;
@@ -155,6 +156,9 @@ k_dht_cols_regs(GridArgs g, const Slot* __restrict__ slots, Tables tb, int stage
     unsigned grp = blockIdx.x, base;
     bool valid;
     load(grp, valid, base);
+    loads_issued();
+    if (mode == 0 && IterView<T>::skip(s.st, stage)) return;
+    twl.store(tw);
     // the line stays in registers; LDS only for the transpose of the
     // transform and the exchange of the (k, N-k) partners, which stays
     // within the wave (reg_col, exchange_write)
@@ -426,17 +430,15 @@ k_dht_z_solve(GridArgs g, const Slot* __restrict__ slots, Tables tb, int stage, 
     __shared__ cpx<T> tw[N];
     __shared__ T lzs[N / 2 + 1];  // the scaled z symbol, even in k (see k_dht_z_solve_regs)
     const Slot& s = slots[blockIdx.y];
-    if (mode == 0 && IterView<T>::skip(s.st, stage)) return;
-    const cpx<T>* twg = twiddles<T>(tb, 2);
-    for (int e = threadIdx.x; e < N; e += NT) tw[e] = twg[e];
-    const T sc = symbol_scale<T>(g);
-    for (int e = threadIdx.x; e <= N / 2; e += NT) lzs[e] = symbol<T>(tb, 2)[e] * sc;
+    TwiddleLoad<T, N, NT> twl;
+    twl.load(twiddles<T>(tb, 2));
     POIS_GLOBAL T* Wc = mode == 0 ? IterView<T>(s).W : (POIS_GLOBAL T*)gptr(s.W);  // complex-indexed
     const unsigned nlines = (unsigned)(g.nxh * g.ny), ngroups = (nlines + L - 1) / L;
     const unsigned se = (unsigned)(g.nxh * g.ny);
     const int l = threadIdx.x % L, t = threadIdx.x / L;
     const T* lamx = symbol<T>(tb, 0);
     const T* lamy = symbol<T>(tb, 1);
+    const T sc = symbol_scale<T>(g);
     const T kn = T(g.n) / sc;  // exact: sc is a power of two
     const unsigned lane_off = (unsigned)t * se;
     cpx<T>* ln = lds + l * F::LS;
@@ -451,6 +453,10 @@ k_dht_z_solve(GridArgs g, const Slot* __restrict__ slots, Tables tb, int stage, 
     unsigned grp = ColShape<T, N, L>::first_group(blockIdx.x, gridDim.x), base;
     bool valid;
     load(grp, valid, base);
+    loads_issued();
+    if (mode == 0 && IterView<T>::skip(s.st, stage)) return;
+    twl.store(tw);
+    for (int e = threadIdx.x; e <= N / 2; e += NT) lzs[e] = symbol<T>(tb, 2)[e] * sc;
     __syncthreads();  // twiddles, symbol
     while (true) {
         cpx<T> v[F::E];

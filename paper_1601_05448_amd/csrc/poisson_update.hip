@@ -42,14 +42,9 @@ k_dhtx_update(GridArgs g, const Slot* __restrict__ slots, Tables tb, int stage, 
     __shared__ cpx<T> lds[L * F::LS];
     __shared__ cpx<T> tw[N];
     const Slot& s = slots[blockIdx.y];
-    if (mode != 1 && IterView<T>::skip(s.st, stage)) return;
-    // the update of the last inner evaluation is applied here: the next inner
-    // residual sweep may run (no other block of this launch reads the flag)
-    if constexpr (sizeof(T) == 4)
-        if (mode == 0 && blockIdx.x == 0 && threadIdx.x == 0) s.st->upd_due = 0;
-    const cpx<T>* twg = twiddles<T>(tb, 0);
     const cpx<T>* twc = dct_twiddles<T>(tb);
-    for (int e = threadIdx.x; e < N; e += NT) tw[e] = twg[e];
+    TwiddleLoad<T, N, NT> twl;
+    twl.load(twiddles<T>(tb, 0));
     const POIS_GLOBAL T* W = (mode != 1) ? IterView<T>(s).W : (const POIS_GLOBAL T*)gptr(s.W);
     POIS_GLOBAL T* out;
     if constexpr (sizeof(T) == 8) out = (POIS_GLOBAL T*)gptr(s.p);
@@ -83,6 +78,13 @@ k_dhtx_update(GridArgs g, const Slot* __restrict__ slots, Tables tb, int stage, 
     };
     unsigned grp = blockIdx.x;
     load_w(grp);
+    loads_issued();
+    if (mode != 1 && IterView<T>::skip(s.st, stage)) return;
+    // the update of the last inner evaluation is applied here: the next inner
+    // residual sweep may run (no other block of this launch reads the flag)
+    if constexpr (sizeof(T) == 4)
+        if (mode == 0 && blockIdx.x == 0 && threadIdx.x == 0) s.st->upd_due = 0;
+    twl.store(tw);
     __syncthreads();  // twiddles
     while (true) {
         cpx<T> v[F::E];
