@@ -613,8 +613,8 @@ __device__ __forceinline__ const float* symbol<float>(const Tables& t, int axis)
 
 // A line sweep's first loads (the twiddles, the first line group) are issued before
 // it looks at the solve's state, so that a launch waits for memory once and not
-// twice (0.1-0.2 us of 3.3-4.0 on a 32^3 grid; in the stencil sweeps the early loads
-// cost more registers than they gain, FP32 at 256^3 51 -> 56 us).  A launch with
+// twice (0.1-0.2 us of 3.3-4.0 on a 32^3 grid).  The stencil sweeps look at the state
+// first: early loads gained nothing there.  A launch with
 // nothing to do reads a little and returns.  The fence only keeps the compiler from
 // moving the loads below the branch.
 __device__ __forceinline__ void loads_issued() { asm volatile("" ::: "memory"); }
