@@ -208,14 +208,12 @@ hipError_t launch_correct(const GridArgs& g, const double* p, double* mx, double
                           hipStream_t s);
 
 // Particles and the grid (poisson_particles.hip): out = P(q) per unit volume
-// (ws: particle_workspace_bytes(g, np) bytes of device scratch; the grid is
-// zeroed on s_aux between the two events while the sort runs on s), out_p =
+// (ws: particle_workspace_bytes(g, np) bytes of device scratch), out_p =
 // I(field)(x_p).  *bad_host = 1 when a position is not finite or too far out
-// (then nothing else is written).
+// (then P's output is untouched).  Both return when the work is done.
 size_t particle_workspace_bytes(const GridArgs& g, int np);
 hipError_t launch_deposit(const GridArgs& g, int np, const double* pos, const double* q, double* out, void* ws,
-                          size_t ws_bytes, int* bad_host, hipStream_t s, hipStream_t s_aux, hipEvent_t ev_fork,
-                          hipEvent_t ev_join);
+                          size_t ws_bytes, int* bad_host, hipStream_t s);
 hipError_t launch_interpolate(const GridArgs& g, int np, const double* pos, const double* field, double* out,
                               int* bad_dev, int* bad_host, hipStream_t s);
 
