@@ -14,6 +14,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libpoisson.so")
 SOURCES = ["poisson_resid_f64.hip", "poisson_resid_f32.hip", "poisson_columns_f64.hip", "poisson_columns_f32.hip",
+           "poisson_planes_f64.hip", "poisson_planes_f32.hip",
            "poisson_update.hip", "poisson_outer.hip", "poisson_sweeps.hip", "poisson_kernels.hip", "poisson_engine.hip",
            "poisson_server.hip", "poisson_project.hip", "poisson_particles.hip", "poisson_noalloc.hip"]
 ARCH = "gfx950"

@@ -518,44 +518,52 @@ static hipError_t col_shape(unsigned nlines, Go&& go) {
     return go.template operator()<narrow_lines<T, N>()>();
 }
 
-template <typename T>
+template <typename T, bool SHORT>
 hipError_t launch_cols_y(const GridArgs& g, const Tables& t, const Slot* slots, int nslots, int mode, hipStream_t s,
                          float share, int stage) {
     return dispatch_len(g.ny, [&]<int N>() {
-        const unsigned nlines = (unsigned)(g.nxh * g.nz);
-        auto run = [&](auto kernel, int nt, int lines) {
-            const void* k = (const void*)kernel;
-            const int nb = persistent_grid(k, nt, (nlines + lines - 1) / lines, nslots, share);
-            kernel<<<dim3(nb, nslots), nt, reserve_lds(k, share), s>>>(g, slots, t, stage, mode);
-            return hipGetLastError();
-        };
-        if constexpr (N == 256 || N == 512)
-            if (nlines / 16 >= kWideGroups) return run(&k_dht_cols_regs<T, N>, LineCfg<T, N>::NT, 16);
-        return col_shape<T, N>(nlines, [&]<int L>() {
-            return run(&k_dht_cols<T, N, L>, ColShape<T, N, L>::NT, L);
-        });
+        if constexpr ((N <= kShortLine) != SHORT) {
+            return hipErrorInvalidValue;
+        } else {
+            const unsigned nlines = (unsigned)(g.nxh * g.nz);
+            auto run = [&](auto kernel, int nt, int lines) {
+                const void* k = (const void*)kernel;
+                const int nb = persistent_grid(k, nt, (nlines + lines - 1) / lines, nslots, share);
+                kernel<<<dim3(nb, nslots), nt, reserve_lds(k, share), s>>>(g, slots, t, stage, mode);
+                return hipGetLastError();
+            };
+            if constexpr (N == 256 || N == 512)
+                if (nlines / 16 >= kWideGroups) return run(&k_dht_cols_regs<T, N>, LineCfg<T, N>::NT, 16);
+            return col_shape<T, N>(nlines, [&]<int L>() {
+                return run(&k_dht_cols<T, N, L>, ColShape<T, N, L>::NT, L);
+            });
+        }
     });
 }
 
-template <typename T>
+template <typename T, bool SHORT>
 hipError_t launch_z_solve(const GridArgs& g, const Tables& t, const Slot* slots, int nslots, int mode, hipStream_t s,
                           float share, int stage) {
     return dispatch_len(g.nz, [&]<int N>() {
-        const unsigned nlines = (unsigned)(g.nxh * g.ny);
-        auto run = [&](auto kernel, int nt, int lines) {
-            const void* k = (const void*)kernel;
-            const int nb = persistent_grid(k, nt, (nlines + lines - 1) / lines, nslots, share);
-            kernel<<<dim3(nb, nslots), nt, reserve_lds(k, share), s>>>(g, slots, t, stage, mode);
-            return hipGetLastError();
-        };
-        if constexpr (N == 256 || N == 512)
-            if (nlines / 16 >= kWideGroups) {
-                using Z = ZRegsCfg<T, N>;
-                return run(&k_dht_z_solve_regs<T, N, Z::PF, Z::MINW>, LineCfg<T, N>::NT, 16);
-            }
-        return col_shape<T, N>(nlines, [&]<int L>() {
-            return run(&k_dht_z_solve<T, N, L>, ColShape<T, N, L>::NT, L);
-        });
+        if constexpr ((N <= kShortLine) != SHORT) {
+            return hipErrorInvalidValue;
+        } else {
+            const unsigned nlines = (unsigned)(g.nxh * g.ny);
+            auto run = [&](auto kernel, int nt, int lines) {
+                const void* k = (const void*)kernel;
+                const int nb = persistent_grid(k, nt, (nlines + lines - 1) / lines, nslots, share);
+                kernel<<<dim3(nb, nslots), nt, reserve_lds(k, share), s>>>(g, slots, t, stage, mode);
+                return hipGetLastError();
+            };
+            if constexpr (N == 256 || N == 512)
+                if (nlines / 16 >= kWideGroups) {
+                    using Z = ZRegsCfg<T, N>;
+                    return run(&k_dht_z_solve_regs<T, N, Z::PF, Z::MINW>, LineCfg<T, N>::NT, 16);
+                }
+            return col_shape<T, N>(nlines, [&]<int L>() {
+                return run(&k_dht_z_solve<T, N, L>, ColShape<T, N, L>::NT, L);
+            });
+        }
     });
 }
 

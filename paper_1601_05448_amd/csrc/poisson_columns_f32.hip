@@ -1,10 +1,11 @@
-// The y and z sweeps on FP32 fields.
+// The y and z sweeps along long lines on FP32 fields.
 #include "poisson_columns.hpp"
 
 namespace pois {
 
-template hipError_t launch_cols_y<float>(const GridArgs&, const Tables&, const Slot*, int, int, hipStream_t, float, int);
-template hipError_t launch_z_solve<float>(const GridArgs&, const Tables&, const Slot*, int, int, hipStream_t, float,
-                                         int);
+template hipError_t launch_cols_y<float, false>(const GridArgs&, const Tables&, const Slot*, int, int, hipStream_t, float,
+                                                int);
+template hipError_t launch_z_solve<float, false>(const GridArgs&, const Tables&, const Slot*, int, int, hipStream_t, float,
+                                                 int);
 
 }  // namespace pois

@@ -162,6 +162,10 @@ hipError_t launch_sweep(const GridArgs& g, const Tables& t, const Slot* slots, i
 // stays as it is).
 hipError_t launch_sweep_mode(const GridArgs& g, const Tables& t, const Slot* slots, int nslots, bool fp32, int which,
                              int mode, hipStream_t s, float share = 1.0f, int stage = 1, bool decide = true);
+// Sweep number of the launch that does P2, P3 and P4 at once, and the grids that
+// have it (k_dht_planes: the same results).
+constexpr int kSweepPlanes = 234;
+bool planes_fusable(const GridArgs& g, int nslots);
 unsigned sweep_groups_x(const GridArgs& g);
 // FP32_REFINE: whether rows of this length take the outer residual fused with
 // the first inner sweep's residual (one marching column per thread), and that

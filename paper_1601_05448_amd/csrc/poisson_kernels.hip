@@ -405,10 +405,14 @@ static hipError_t five_sweeps(const GridArgs& g, const Tables& t, const Slot* sl
     };
     if ((parts & 1) && (e = sweep(1)) != hipSuccess) return e;
     if (!(parts & 2)) return hipSuccess;
-    if ((e = sweep(2)) != hipSuccess) return e;
-    if ((e = sweep(3)) != hipSuccess) return e;
-    if ((e = sweep(2)) != hipSuccess) return e;
-    return sweep(5);
+    // a timed y or z sweep runs by itself
+    if (planes_fusable(g, nslots) && !(tm && tm->fp32 == fp32 && (tm->sweep == 2 || tm->sweep == 3))) {
+        if ((e = sweep(kSweepPlanes)) != hipSuccess) return e;
+        return sweep(5);
+    }
+    for (int which : {2, 3, 2, 5})
+        if ((e = sweep(which)) != hipSuccess) return e;
+    return hipSuccess;
 }
 
 hipError_t launch_sweep(const GridArgs& g, const Tables& t, const Slot* slots, int nslots, bool fp32, int which,
@@ -448,9 +452,13 @@ hipError_t launch_outer_resid_sweep(const GridArgs& g, const Slot* slots, int ns
 hipError_t launch_outer_tail(const GridArgs& g, const Geometry& geo, const Tables& t, const Slot* slots,
                              int nslots, hipStream_t s) {
     hipError_t e;
+    auto sweep = [&](int which) { return launch_sweep_mode(g, t, slots, nslots, true, which, 0, s, geo.share, kStageTail); };
+    if (planes_fusable(g, nslots)) {
+        if ((e = sweep(kSweepPlanes)) != hipSuccess) return e;
+        return sweep(5);
+    }
     for (int which : {2, 3, 2, 5})
-        if ((e = launch_sweep_mode(g, t, slots, nslots, true, which, 0, s, geo.share, kStageTail)) != hipSuccess)
-            return e;
+        if ((e = sweep(which)) != hipSuccess) return e;
     return hipSuccess;
 }
 

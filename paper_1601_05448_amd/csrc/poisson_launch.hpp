@@ -22,12 +22,19 @@ constexpr unsigned kWideGroups = 512;
 template <typename T>
 hipError_t launch_resid(const GridArgs& g, const Tables& t, const Slot* slots, int nslots, int mode, hipStream_t s,
                         float share, bool decide);
-template <typename T>
+// (Lines of up to kShortLine apart from longer ones: they are compiled with
+// k_dht_planes, see poisson_planes_f32.hip.)
+constexpr int kShortLine = 64;
+template <typename T, bool SHORT>
 hipError_t launch_cols_y(const GridArgs& g, const Tables& t, const Slot* slots, int nslots, int mode, hipStream_t s,
                          float share, int stage);
-template <typename T>
+template <typename T, bool SHORT>
 hipError_t launch_z_solve(const GridArgs& g, const Tables& t, const Slot* slots, int nslots, int mode, hipStream_t s,
                           float share, int stage);
+// P2, P3 and P4 as one launch, for grids with planes_fusable.
+template <typename T>
+hipError_t launch_planes(const GridArgs& g, const Tables& t, const Slot* slots, int nslots, int mode, hipStream_t s,
+                         float share, int stage);
 template <typename T>
 hipError_t launch_update(const GridArgs& g, const Tables& t, const Slot* slots, int nslots, int mode, hipStream_t s,
                          float share, int stage);

@@ -142,8 +142,13 @@ static hipError_t sweep_t(const GridArgs& g, const Tables& t, const Slot* slots,
                           hipStream_t s, float share, int stage, bool decide) {
     switch (which) {
         case 1: return launch_resid<T>(g, t, slots, nslots, mode, s, share, decide);
-        case 2: return launch_cols_y<T>(g, t, slots, nslots, mode, s, share, stage);
-        case 3: return launch_z_solve<T>(g, t, slots, nslots, mode, s, share, stage);
+        case 2:
+            return g.ny <= kShortLine ? launch_cols_y<T, true>(g, t, slots, nslots, mode, s, share, stage)
+                                      : launch_cols_y<T, false>(g, t, slots, nslots, mode, s, share, stage);
+        case 3:
+            return g.nz <= kShortLine ? launch_z_solve<T, true>(g, t, slots, nslots, mode, s, share, stage)
+                                      : launch_z_solve<T, false>(g, t, slots, nslots, mode, s, share, stage);
+        case kSweepPlanes: return launch_planes<T>(g, t, slots, nslots, mode, s, share, stage);
         case 5: return launch_update<T>(g, t, slots, nslots, mode, s, share, stage);
         default: return hipErrorInvalidValue;
     }
@@ -154,6 +159,19 @@ hipError_t launch_sweep_mode(const GridArgs& g, const Tables& t, const Slot* slo
     if (mode == 1) stage = 1;
     return fp32 ? sweep_t<float>(g, t, slots, nslots, which, mode, s, share, stage, decide)
                 : sweep_t<double>(g, t, slots, nslots, which, mode, s, share, 1, decide);
+}
+
+// Planes of up to 48 x 48 values while the launch's columns are few: a larger
+// plane's chain of transforms, or many columns' access (16 or 8 bytes per row),
+// takes longer than the sweeps it replaces.  The bits are the same either way, so
+// the batch may decide.  Whole solves, three launches / one, us: FP64 32^3
+// 411 / 358, 24 x 48 x 64 430 / 381, 48^3 429 / 417, 32 x 64 x 64 426 / 400, 48 x 48 x
+// 512 741 / 725 (but x 1024 944 / 981, and 64^3 403 / 426); FP32 + refinement 434 /
+// 386, 457 / 405, 449 / 432, 453 / 416, 619 / 618 (but 64^3 465 / 480, and 40 served
+// ones 4861 / 6560).
+bool planes_fusable(const GridArgs& g, int nslots) {
+    if (g.ny < 16 || g.ny > 64 || g.nz < 16 || g.nz > 64) return false;
+    return g.ny * g.nz <= 48 * 48 && (long long)g.ny * g.nz * g.nxh * nslots <= 48 * 48 * 256;
 }
 
 unsigned sweep_groups_x(const GridArgs& g) {

@@ -32,7 +32,7 @@ import statistics
 import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-KERNEL_SOURCES = ("poisson_sweeps.hip", "poisson_resid.hpp", "poisson_outer.hip", "poisson_columns.hpp",
+KERNEL_SOURCES = ("poisson_sweeps.hip", "poisson_resid.hpp", "poisson_outer.hip", "poisson_columns.hpp", "poisson_planes.hpp",
                   "poisson_update.hip", "poisson_rows.hpp", "poisson_launch.hpp", "poisson_device.hpp", "poisson_fft.hpp",
                   "poisson_internal.hpp", "poisson_kernels.hip", "poisson_control.hpp")
 
