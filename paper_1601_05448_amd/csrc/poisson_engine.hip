@@ -219,31 +219,13 @@ Slot Workspace::slot(const double* rho, const double* b, double* p, double tol) 
 
 // ---- the solve driver -----------------------------------------------------------------
 
-// n values of T, on the stack for small batches (a single solve allocates
-// nothing on the host), on the heap for large ones.
-template <class T>
-struct SmallArray {
-    static constexpr int kLocal = 64;
-    T local[kLocal];
-    std::vector<T> heap;
-    T* v;
-    SmallArray(int n, T init) : v(local) {
-        if (n > kLocal) {
-            heap.assign((size_t)n, init);
-            v = heap.data();
-        } else {
-            for (int q = 0; q < n; ++q) local[q] = init;
-        }
-    }
-    T& operator[](int q) { return v[q]; }
-};
-
-// Enqueue the whole solve for the slots on the stream, reading back the state
-// header of slot 0..nslots-1 between chunks.  `hdr` is pinned host memory for
-// nslots state headers.
-int drive_solve(const GridArgs& g, const Geometry& geo, const Tables& t, const Slot* d_slots, int nslots,
-                SolveState* const* d_states, SolveState* hdr, const SolveParams& prm, hipStream_t s,
-                SweepTimer* tm, GraphCache* gc) {
+// Runs the whole solve of `slot` on the stream and returns when it is done, with
+// its state in *st_host.  The device copy of the slot is written by the solve's
+// first kernel.  `end`, where given, is recorded after the solve's last work.
+int drive_solve(const GridArgs& g, const Geometry& geo, const Tables& t, const Slot& slot, Slot* d_slots,
+                SolveState* st_host, const SolveParams& prm, hipStream_t s, hipEvent_t end, SweepTimer* tm,
+                GraphCache* gc) {
+    constexpr int nslots = 1;
     hipError_t e;
     // n iterations: replayed graphs of 16, 8, 4, 2, 1 iterations when a graph
     // cache is given (and no timer brackets single launches), else direct launches
@@ -270,22 +252,22 @@ int drive_solve(const GridArgs& g, const Geometry& geo, const Tables& t, const S
         return hipSuccess;
     };
     const bool fp32 = prm.precision == POISSON_FP32_REFINE;
-    if ((e = launch_init(g, d_slots, nslots, prm.inner_tol, prm.max_iter, prm.max_outer, prm.precision, s)) !=
+    if ((e = launch_init_slot(slot, d_slots, prm.inner_tol, prm.max_iter, prm.max_outer, prm.precision, s)) !=
         hipSuccess)
         return hip_status(e);
     if ((e = launch_setup(g, geo, d_slots, nslots, fp32, s)) != hipSuccess) return hip_status(e);
-    const size_t hb = offsetof(SolveState, hist);
-    bool all_done = false;
-    auto poll = [&]() -> int {  // 1: all done, 0: not yet, <0 error
-        for (int q = 0; q < nslots; ++q)
-            if ((e = hipMemcpyAsync(&hdr[q], d_states[q], hb, hipMemcpyDeviceToHost, s)) != hipSuccess)
-                return hip_status(e);
+    const SolveState& h = *st_host;
+    // A poll reads the whole state (2.5 KB), so that the poll that finds the solve
+    // done is the solve's last copy and synchronisation.  1: done, 0: not yet, <0
+    // error.  (An iteration enqueued behind the copy hides the host's look at it,
+    // 6% of a 32^3 solve, but a solve that the first poll finds done then waits
+    // for it to idle: 128^3 156 -> 175 us.)
+    auto poll = [&]() -> int {
+        if (end && (e = hipEventRecord(end, s)) != hipSuccess) return hip_status(e);
+        if ((e = hipMemcpyAsync(st_host, slot.st, sizeof(SolveState), hipMemcpyDeviceToHost, s)) != hipSuccess)
+            return hip_status(e);
         if ((e = hipStreamSynchronize(s)) != hipSuccess) return hip_status(e);
-        for (int q = 0; q < nslots; ++q) {
-            if (!hdr[q].done) return 0;
-        }
-        all_done = true;
-        return 1;
+        return h.done ? 1 : 0;
     };
     if (!fp32) {
         // Chunks of iterations between polls.  After the first chunk the next
@@ -294,8 +276,8 @@ int drive_solve(const GridArgs& g, const Geometry& geo, const Tables& t, const S
         // quarter of one (an idle launch costs less than another poll).
         int launched = 0, chunk = prm.first_chunk;
         const int cap = prm.max_iter + 1;
-        SmallArray<int> k_prev(nslots, -1);
-        SmallArray<double> r_prev(nslots, 0.0);
+        int k_prev = -1;
+        double r_prev = 0.0;
         while (true) {
             const int now = std::min(chunk, cap - launched);
             if ((e = iterations(now, false)) != hipSuccess) return hip_status(e);
@@ -303,23 +285,17 @@ int drive_solve(const GridArgs& g, const Geometry& geo, const Tables& t, const S
             const int r = poll();
             if (r < 0) return r;
             if (r == 1 || launched >= cap) break;
-            int need = 0;
-            for (int q = 0; q < nslots; ++q) {
-                const SolveState& h = hdr[q];
-                if (h.done) continue;
-                const int k = h.iter - 1;  // index of the last residual evaluated
-                double rate = 1.0;
-                if (k_prev[q] >= 0 && k > k_prev[q] && r_prev[q] > 0.0)
-                    rate = std::pow(h.rel / r_prev[q], 1.0 / (k - k_prev[q]));
-                else if (k >= 1 && h.rel0 > 0.0)
-                    rate = std::pow(h.rel / h.rel0, 1.0 / k);
-                k_prev[q] = k;
-                r_prev[q] = h.rel;
-                int m = 2 * chunk;
-                if (rate > 0.0 && rate < 0.95 && h.rel > 0.0)
-                    m = (int)std::ceil(std::log(h.tol / h.rel) / std::log(rate) + 0.25);
-                need = std::max(need, m);
-            }
+            const int k = h.iter - 1;  // index of the last residual evaluated
+            double rate = 1.0;
+            if (k_prev >= 0 && k > k_prev && r_prev > 0.0)
+                rate = std::pow(h.rel / r_prev, 1.0 / (k - k_prev));
+            else if (k >= 1 && h.rel0 > 0.0)
+                rate = std::pow(h.rel / h.rel0, 1.0 / k);
+            k_prev = k;
+            r_prev = h.rel;
+            int need = 2 * chunk;
+            if (rate > 0.0 && rate < 0.95 && h.rel > 0.0)
+                need = (int)std::ceil(std::log(h.tol / h.rel) / std::log(rate) + 0.25);
             chunk = std::clamp(need, 1, prm.max_chunk);
         }
     } else {
@@ -400,54 +376,50 @@ int drive_solve(const GridArgs& g, const Geometry& geo, const Tables& t, const S
             // round and a long one a few idle launches.
             int need_open = 0, need_full = 0, need_steps = 0, need_last = 0;
             bool need_tail = false, need_update = false;
-            for (int q = 0; q < nslots; ++q) {
-                const SolveState& h = hdr[q];
-                if (h.done) continue;
-                double red = h.rel_in;  // outer reduction per step
-                double rel = h.rel;     // outer residual before the next outer evaluation
-                if (h.stage == kStageTail) {
-                    // a step's first sweep still open (not left by the launch
-                    // sequences above, which follow every fused outer residual
-                    // with its tail): it goes on
-                    need_tail = true;
-                    need_open = std::max(need_open, std::max(full, 1));
-                    red = h.inner_goal;
-                } else if (h.stage != 0) {
-                    int m = 2 * std::max(std::max(full, open_full), 1);
-                    const int k = h.inner_iter - 1;  // index of the last inner residual evaluated
-                    if (k >= 1 && h.rel_in > 0.0 && h.rel_in < 1.0) {
-                        const double rate = std::pow(h.rel_in, 1.0 / k);
-                        if (rate < 0.95) m = (int)std::ceil(std::log(h.inner_goal / h.rel_in) / std::log(rate) + 0.25);
-                    }
-                    // the phase ends after the pending update: one evaluation closes it
-                    if (h.stop_next) m = 1;
-                    if (h.stage == 1 && h.upd_due) need_update = true;
-                    need_open = std::max(need_open, std::max(m, 1));
-                    red = h.inner_goal;
-                } else {
-                    need_full = std::max(need_full, h.inner_last - first);
+            double red = h.rel_in;  // outer reduction per step
+            double rel = h.rel;     // outer residual before the next outer evaluation
+            if (h.stage == kStageTail) {
+                // a step's first sweep still open (not left by the launch
+                // sequences above, which follow every fused outer residual
+                // with its tail): it goes on
+                need_tail = true;
+                need_open = std::max(need_open, std::max(full, 1));
+                red = h.inner_goal;
+            } else if (h.stage != 0) {
+                int m = 2 * std::max(std::max(full, open_full), 1);
+                const int k = h.inner_iter - 1;  // index of the last inner residual evaluated
+                if (k >= 1 && h.rel_in > 0.0 && h.rel_in < 1.0) {
+                    const double rate = std::pow(h.rel_in, 1.0 / k);
+                    if (rate < 0.95) m = (int)std::ceil(std::log(h.inner_goal / h.rel_in) / std::log(rate) + 0.25);
                 }
-                const double redc = std::clamp(red, 1e-12, 0.5);
-                // in stage 0 the last update has not been measured yet (one
-                // reduction pending), except after a check that did not end the
-                // solve: its residual is that of the current p, and at least one
-                // more step is due
-                if (!(h.stage == 0 && h.checked)) rel *= redc;
-                int st = 0;
-                if (rel > 0.5 * h.tol) st = (int)std::ceil(std::log(0.5 * h.tol / rel) / std::log(redc));
-                st = std::clamp(st, 0, 8);
-                need_steps = std::max(need_steps, st);
-                // the last predicted step: from rel redc^(st-1), it needs the
-                // inner reduction max(inner tol, 0.8 tol / that)
-                int last = h.inner_last - first;
-                if (h.stage == 0 && st >= 1 && h.inner_last >= 2 && h.rel_in > 0.0 && h.rel_in < 1.0) {
-                    const double rate = std::pow(h.rel_in, 1.0 / (h.inner_last - 1));
-                    const double goal = std::max(h.inner_tol, 0.8 * h.tol / (rel * std::pow(redc, st - 1)));
-                    if (rate < 0.95 && goal < 1.0)
-                        last = (int)std::ceil(std::log(goal) / std::log(rate)) + 1 - first;
-                }
-                need_last = std::max(need_last, last);
+                // the phase ends after the pending update: one evaluation closes it
+                if (h.stop_next) m = 1;
+                if (h.stage == 1 && h.upd_due) need_update = true;
+                need_open = std::max(need_open, std::max(m, 1));
+                red = h.inner_goal;
+            } else {
+                need_full = std::max(need_full, h.inner_last - first);
             }
+            const double redc = std::clamp(red, 1e-12, 0.5);
+            // in stage 0 the last update has not been measured yet (one
+            // reduction pending), except after a check that did not end the
+            // solve: its residual is that of the current p, and at least one
+            // more step is due
+            if (!(h.stage == 0 && h.checked)) rel *= redc;
+            int st = 0;
+            if (rel > 0.5 * h.tol) st = (int)std::ceil(std::log(0.5 * h.tol / rel) / std::log(redc));
+            st = std::clamp(st, 0, 8);
+            need_steps = std::max(need_steps, st);
+            // the last predicted step: from rel redc^(st-1), it needs the
+            // inner reduction max(inner tol, 0.8 tol / that)
+            int last = h.inner_last - first;
+            if (h.stage == 0 && st >= 1 && h.inner_last >= 2 && h.rel_in > 0.0 && h.rel_in < 1.0) {
+                const double rate = std::pow(h.rel_in, 1.0 / (h.inner_last - 1));
+                const double goal = std::max(h.inner_tol, 0.8 * h.tol / (rel * std::pow(redc, st - 1)));
+                if (rate < 0.95 && goal < 1.0)
+                    last = (int)std::ceil(std::log(goal) / std::log(rate)) + 1 - first;
+            }
+            need_last = std::max(need_last, last);
             open_full = std::min(need_open, prm.max_chunk);
             open_tail = need_tail;
             open_update = need_update;
@@ -457,10 +429,18 @@ int drive_solve(const GridArgs& g, const Geometry& geo, const Tables& t, const S
             check = true;
         }
     }
-    // the rounds ran out before every solve reached a terminal status: those
-    // end as if capped (p is their last iterate)
-    if (!all_done && (e = launch_stop_unfinished(d_slots, nslots, s)) != hipSuccess) return hip_status(e);
-    if ((e = launch_fixup(g, geo, d_slots, nslots, s)) != hipSuccess) return hip_status(e);
+    // the rounds ran out before the solve reached a terminal status: it ends as
+    // if capped (p is its last iterate)
+    if (!h.done) {
+        if ((e = launch_stop_unfinished(d_slots, nslots, s)) != hipSuccess) return hip_status(e);
+        const int r = poll();
+        if (r < 0) return r;
+    }
+    if (fixup_due(h)) {  // (leaves the state as it is)
+        if ((e = launch_fixup(g, geo, d_slots, nslots, s)) != hipSuccess) return hip_status(e);
+        if (end && (e = hipEventRecord(end, s)) != hipSuccess) return hip_status(e);
+        if ((e = hipStreamSynchronize(s)) != hipSuccess) return hip_status(e);
+    }
     return POISSON_OK;
 }
 
@@ -605,12 +585,10 @@ static bool overlaps(const void* a, size_t na, const void* b, size_t nb) {
     return na > 0 && nb > 0 && x < y + nb && y < x + na;
 }
 
-static int set_slot(poisson_t h, const Slot& s, hipStream_t st) {
+static int set_slot(poisson_t h, const Slot& s) {
     *h->h_slot = s;
-    return hip_status(hipMemcpyAsync(h->d_slot, h->h_slot, sizeof(Slot), hipMemcpyHostToDevice, st));
+    return hip_status(hipMemcpyAsync(h->d_slot, h->h_slot, sizeof(Slot), hipMemcpyHostToDevice, h->stream));
 }
-
-static int set_slot(poisson_t h, const Slot& s) { return set_slot(h, s, h->stream); }
 
 int poisson_solve(poisson_t h, const double* rho, const double* b, double* p, double tol) {
     if (!h || !rho || !b || !p || !(tol > 0.0) || !std::isfinite(tol)) return POISSON_EINVAL;
@@ -619,7 +597,6 @@ int poisson_solve(poisson_t h, const double* rho, const double* b, double* p, do
     // the solve runs on the library's stream, after the caller's earlier work
     int rc = hip_status(hipEventRecord(h->ev_in, h->stream));
     if (rc == POISSON_OK) rc = hip_status(hipStreamWaitEvent(h->run, h->ev_in, 0));
-    if (rc == POISSON_OK) rc = set_slot(h, h->ws.slot(rho, b, p, tol), h->run);
     if (rc != POISSON_OK) return rc;
     SolveParams prm;
     prm.tol = tol;
@@ -627,16 +604,11 @@ int poisson_solve(poisson_t h, const double* rho, const double* b, double* p, do
     prm.max_iter = h->o.max_iter;
     prm.inner_tol = h->o.inner_tol;
     if ((rc = hip_status(hipEventRecord(h->ev0, h->run))) != POISSON_OK) return rc;
-    SolveState* dst = h->ws.st;
     h->timer.used = 0;
-    rc = drive_solve(h->g, h->geo, h->tables.t, h->d_slot, 1, &dst, h->h_state, prm, h->run,
-                     h->timer.sweep ? &h->timer : nullptr, h->o.use_graphs ? &h->graphs : nullptr);
+    rc = drive_solve(h->g, h->geo, h->tables.t, h->ws.slot(rho, b, p, tol), h->d_slot, h->h_state, prm, h->run,
+                     h->ev1, h->timer.sweep ? &h->timer : nullptr,
+                     h->o.use_graphs ? &h->graphs : nullptr);
     if (rc != POISSON_OK) return rc;
-    if ((rc = hip_status(hipEventRecord(h->ev1, h->run))) != POISSON_OK) return rc;
-    if ((rc = hip_status(hipMemcpyAsync(h->h_state, h->ws.st, sizeof(SolveState), hipMemcpyDeviceToHost,
-                                        h->run))) != POISSON_OK)
-        return rc;
-    if ((rc = hip_status(hipStreamSynchronize(h->run))) != POISSON_OK) return rc;
     const SolveState& st = *h->h_state;
     fill_stats(h->g, st, &h->stats);
     float ms = 0.f;

@@ -93,8 +93,8 @@ bool valid_lengths(double lx, double ly, double lz);
 GridArgs make_grid(int nx, int ny, int nz, double lx, double ly, double lz, int coef, int weight, int bcx = 0);
 double min_symbol(const GridArgs& g);
 size_t workspace_bytes(const GridArgs& g, const Geometry& geo, int precision);
-int drive_solve(const GridArgs& g, const Geometry& geo, const Tables& t, const Slot* d_slots, int nslots,
-                SolveState* const* d_states, SolveState* hdr, const SolveParams& prm, hipStream_t s,
+int drive_solve(const GridArgs& g, const Geometry& geo, const Tables& t, const Slot& slot, Slot* d_slots,
+                SolveState* st_host, const SolveParams& prm, hipStream_t s, hipEvent_t end = nullptr,
                 SweepTimer* tm = nullptr, GraphCache* gc = nullptr);
 void fill_stats(const GridArgs& g, const SolveState& st, poisson_stats* out);
 

@@ -86,6 +86,16 @@ struct SolveState {
     double hist[kHistCap];
 };
 
+// What a finished solve leaves to k_fixup: p = 0 where b - mean(b) is 0, and the
+// mean of the incoming p, which the first update removes, where none ran (iter ==
+// 0 on both paths).
+__host__ __device__ inline bool solution_is_zero(const SolveState& st) {
+    return st.b_norm == 0.0 && st.done && st.status == POISSON_OK;
+}
+__host__ __device__ inline bool fixup_due(const SolveState& st) {
+    return st.status != POISSON_EDOMAIN && (solution_is_zero(st) || (st.iter == 0 && st.p_shift != 0.0));
+}
+
 // Per-solve device pointers (a batch launch indexes these by blockIdx.y).
 struct Slot {
     double tol;       // relative-residual target of this solve
@@ -128,6 +138,8 @@ Geometry make_geometry(const GridArgs& g);
 bool length_supported(int n);
 
 // Initialises the state of each slot (tolerance from Slot::tol).
+hipError_t launch_init_slot(const Slot& slot, Slot* slots, double inner_tol, int max_iter, int max_outer,
+                            int precision, hipStream_t s);
 hipError_t launch_init(const GridArgs& g, const Slot* slots, int nslots, double inner_tol, int max_iter,
                        int max_outer, int precision, hipStream_t s);
 hipError_t launch_setup(const GridArgs& g, const Geometry& geo, const Slot* slots, int nslots,

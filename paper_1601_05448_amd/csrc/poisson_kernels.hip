@@ -32,17 +32,17 @@ namespace pois {
 
 constexpr int kPtThreads = 256;
 
-__global__ void __launch_bounds__(256) k_init(const Slot* __restrict__ slots, double inner_tol, int max_iter,
-                                             int max_outer, int precision) {
-    SolveState* st = slots[blockIdx.x].st;
+__device__ __forceinline__ void init_state(const Slot& s, double inner_tol, int max_iter, int max_outer,
+                                           int precision) {
+    SolveState* st = s.st;
     // zero the whole record with vector stores, then set the parameters
     unsigned long long* w = reinterpret_cast<unsigned long long*>(st);
     constexpr int words = (int)(sizeof(SolveState) / sizeof(unsigned long long));
     for (int q = threadIdx.x; q < words; q += 256) w[q] = 0ull;
-    if (threadIdx.x < kArriveGroups) *arrive_group(slots[blockIdx.x].partial, threadIdx.x) = 0u;
+    if (threadIdx.x < kArriveGroups) *arrive_group(s.partial, threadIdx.x) = 0u;
     __syncthreads();
     if (threadIdx.x != 0) return;
-    st->tol = slots[blockIdx.x].tol;
+    st->tol = s.tol;
     st->inner_tol = inner_tol;
     st->inner_goal = inner_tol;
     st->max_iter = max_iter;
@@ -50,6 +50,19 @@ __global__ void __launch_bounds__(256) k_init(const Slot* __restrict__ slots, do
     st->precision = precision;
     st->status = POISSON_OK;
     st->inv_s = 1.0;
+}
+
+__global__ void __launch_bounds__(256) k_init(const Slot* __restrict__ slots, double inner_tol, int max_iter,
+                                             int max_outer, int precision) {
+    init_state(slots[blockIdx.x], inner_tol, max_iter, max_outer, precision);
+}
+
+// The same for one slot that the host passes by value and the kernel puts in
+// place: no copy of its own before it.
+__global__ void __launch_bounds__(256) k_init_slot(Slot slot, Slot* __restrict__ slots, double inner_tol,
+                                                  int max_iter, int max_outer, int precision) {
+    if (threadIdx.x == 0) slots[0] = slot;
+    init_state(slot, inner_tol, max_iter, max_outer, precision);
 }
 
 __device__ double pow2_near(double x) {
@@ -312,12 +325,8 @@ __global__ void __launch_bounds__(kPtThreads) k_outer_update(GridArgs g, const S
 __global__ void __launch_bounds__(kPtThreads) k_fixup(GridArgs g, const Slot* __restrict__ slots) {
     const Slot& s = slots[blockIdx.y];
     const SolveState* st = s.st;
-    if (st->status == POISSON_EDOMAIN) return;
-    const bool zero = st->b_norm == 0.0 && st->done && st->status == POISSON_OK;
-    // the first update removes p_shift; a solve that ends before any update
-    // (iter == 0 on both paths) still has to
-    const bool shift_left = st->iter == 0 && st->p_shift != 0.0;
-    if (!zero && !shift_left) return;
+    if (!fixup_due(*st)) return;
+    const bool zero = solution_is_zero(*st);
     const double sh = st->p_shift;
     const long long stride = (long long)gridDim.x * kPtThreads;
     for (long long c = (long long)blockIdx.x * kPtThreads + threadIdx.x; c < g.n; c += stride)
@@ -374,6 +383,12 @@ hipError_t launch_init(const GridArgs& g, const Slot* slots, int nslots, double 
                        int max_outer, int precision, hipStream_t s) {
     (void)g;
     k_init<<<nslots, 256, 0, s>>>(slots, inner_tol, max_iter, max_outer, precision);
+    return hipGetLastError();
+}
+
+hipError_t launch_init_slot(const Slot& slot, Slot* slots, double inner_tol, int max_iter, int max_outer,
+                            int precision, hipStream_t s) {
+    k_init_slot<<<1, 256, 0, s>>>(slot, slots, inner_tol, max_iter, max_outer, precision);
     return hipGetLastError();
 }
 

@@ -38,11 +38,10 @@ constexpr int kMaxDevices = 64;
 
 // Host state of the entry point, guarded by g_mu: the device address of
 // `scratch` per device, and pageable host staging (no allocation) for the
-// tables, the slot record and the state read back.
+// tables and the state read back.
 std::mutex g_mu;
 void* g_scratch[kMaxDevices] = {};
 alignas(256) unsigned char g_tables_host[kTablesHostBytes];
-Slot g_slot_host;
 SolveState g_state_host;
 
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
@@ -107,22 +106,14 @@ int poisson_solve_noalloc(const poisson_opts* o, const double* rho, const double
     const Tables tables = bind_tables(g, base);
     Workspace ws;
     ws.carve(g, geo, o->precision, base + off_ws);
-    g_slot_host = ws.slot(rho, b, p, tol);
     Slot* d_slot = reinterpret_cast<Slot*>(base + off_slot);
-    if ((e = hipMemcpyAsync(d_slot, &g_slot_host, sizeof(Slot), hipMemcpyHostToDevice, s)) != hipSuccess)
-        return hip_status(e);
-
     SolveParams prm;
     prm.tol = tol;
     prm.precision = o->precision;
     prm.max_iter = o->max_iter > 0 ? o->max_iter : 1000;
     prm.inner_tol = o->inner_tol > 0.0 ? o->inner_tol : 5e-4;
-    SolveState* st_dev = ws.st;
-    rc = drive_solve(g, geo, tables, d_slot, 1, &st_dev, &g_state_host, prm, s, nullptr, nullptr);
+    rc = drive_solve(g, geo, tables, ws.slot(rho, b, p, tol), d_slot, &g_state_host, prm, s);
     if (rc != POISSON_OK) return rc;
-    if ((e = hipMemcpyAsync(&g_state_host, ws.st, sizeof(SolveState), hipMemcpyDeviceToHost, s)) != hipSuccess)
-        return hip_status(e);
-    if ((e = hipStreamSynchronize(s)) != hipSuccess) return hip_status(e);
     poisson_stats out{};
     fill_stats(g, g_state_host, &out);
     out.ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
