@@ -80,8 +80,8 @@ __global__ void __launch_bounds__(kPartThreads) k_part_flag_clear(int* __restric
 // bits: three of 9).  Latency bounds it, not traffic (8 MB of pairs per pass at
 // 10^6), so the loads of a tile are all issued at once, the counts lie tile-major
 // (every access of them is coalesced; digit-major they were 10^6 four-byte
-// stores), and a wave ranks its pairs without a barrier.  10^6 pairs: 28 us per pass
-// (count 4, scan 7, scatter 17), where it was 98 us (35, 23 and 5, 35).
+// stores), and a wave ranks its pairs without a barrier.  10^6 pairs: 24 us per pass
+// (count 4, scan 5, scatter 15), where it was 98 us (35, 23 and 5, 35).
 constexpr int kDigitBits = 10;
 constexpr int kDigits = 1 << kDigitBits;
 constexpr int kSortThreads = 256;
@@ -343,10 +343,10 @@ __device__ __forceinline__ int first_between(const uint2* __restrict__ pair, int
 // per block and the planes in turn: 381 us for 10^6 particles on 512^3).  Filling
 // the grid with zeros and adding the runs in eight passes (one per parity class
 // of the run's cell) moved whole lines both ways for 8-byte updates: 172 us of
-// filling beside the sort and 267 us of passes after it, now 274 us in all (3.9
+// filling beside the sort and 267 us of passes after it, now 255 us in all (4.2
 // TB/s of the grid's 1.07 GB).  Deposits, before and after: 10^6 particles on
-// 512^3 746 -> 444 us (10^4 of them in one cell 1264 -> 657, all of them 53.5 ->
-// 22.1 ms), 2 10^6 on 256^3 647 -> 317, 2000 on 32^3 160 -> 96.
+// 512^3 746 -> 416 us (10^4 of them in one cell 1264 -> 634, all of them 53.5 ->
+// 22.1 ms), 2 10^6 on 256^3 647 -> 310, 2000 on 32^3 160 -> 80.
 constexpr int kSpanMax = 32;  // tiles of a block at most (their bounds: 512 bytes of LDS)
 
 __global__ void __launch_bounds__(kPartThreads)
@@ -439,13 +439,16 @@ k_part_cells(PartGeom pg, int np, const uint2* __restrict__ pair, const double* 
     }
 }
 
-// Rows of a tile of k_part_cells: up to 16 KB of LDS (eight blocks per CU), fewer
-// where that leaves the chip without four blocks per CU (10^6 particles on 512^3:
-// 491, 444 and 424 us with 8, 16 and 32 KB, 2 10^6 on 256^3: 322, 317, 334); then as many tiles per
-// block as leave eight blocks per CU (fewer would not fill it, more repeat the
-// search for the rows' bounds: with 32 blocks per CU 460 and 337 us).
+// Rows of a tile of k_part_cells: eight, or what fits 32 KB of LDS (five blocks per
+// CU), fewer where that leaves the chip without four blocks per CU.  More rows
+// share the search and the row below the tile (10^6 particles on 512^3: 491, 433
+// and 416 us with 2, 4 and 8 rows; 3 10^5 on 384 x 192 x 768: 240 with 2, 221 with
+// 5), more than eight leave too little work in flight (2 10^6 on 256^3: 317 with 8,
+// 334 with 16).  Then as many tiles per block as leave eight blocks per CU (fewer
+// would not fill it, more repeat the search for the rows' bounds: with 32 blocks
+// per CU 460 us on 512^3 and 337 on 256^3 where it was 444 and 317).
 static int tile_rows(const GridArgs& g) {
-    int rows = std::max(1, std::min(g.ny, 2048 / g.nx));
+    int rows = std::max(1, std::min({g.ny, 8, 4096 / g.nx}));
     while (rows > 1 && (long long)g.nz * ((g.ny + rows - 1) / rows) < 1024) rows = (rows + 1) / 2;
     return rows;
 }
