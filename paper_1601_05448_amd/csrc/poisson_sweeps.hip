@@ -7,20 +7,20 @@
 //   P2 k_dht_cols     Hartley along y of W (also P4: the transform is self-inverse)
 //   P3 k_dht_z_solve  Hartley along z, divide by n * symbol, Hartley along z
 //                     (taken as FFT, scaling of the separated spectra, inverse FFT)
+//   (P2, P3 and P4 of small grids as one launch: k_dht_planes)
 //   P5 k_dhtx_update  Hartley along x, p += dp (minus the mean of p)
 // With walls in x (GridArgs::bcx) P1 and P5 take the cosine transform along x
 // instead of the Hartley transform; P2-P4 are the same.
 // and, for the FP32 refinement, k_outer_resid_dhtx: the FP64 outer residual
 // fused with the first inner sweep's residual.
 //
-// Each block holds L whole lines of its transform direction in LDS.  The LDS a
-// line group needs limits an FP64 sweep to two blocks per CU, too few waves to
-// hide HBM latency by occupancy alone, so the blocks are persistent and
-// software-pipelined: a block loops over line groups, and the global loads of
-// the next group (and, in the FP32 P5, the loads of the values to update) are
-// issued before the FFT of the current group, so that they are in flight while
-// the block works in LDS.  The stencil sweeps keep the next plane's loads in
-// flight while they evaluate the current one, for the same reason.
+// Each block holds whole lines of its transform direction.  The registers and the
+// LDS of a line group leave a sweep two to four waves per SIMD on large grids, too
+// few to hide memory latency by occupancy alone, so the blocks are persistent and
+// software-pipelined: a block loops over line groups, and the global loads of the
+// next group are issued before the FFT of the current group, so that they are in
+// flight while the block works in LDS.  The stencil sweeps keep the next plane's
+// loads in flight while they evaluate the current one, for the same reason.
 //
 // blockIdx.y selects the solve (slot) of a batch of equal-size grids; every sweep
 // returns at once for solves that are done or, on the FP32 path, not in the

@@ -150,8 +150,9 @@ def cmd_bytes(a) -> None:
               f"  {name[:110]}")
 
 
-SWEEP_KERNELS = ("k_resid_dhtx_z", "k_dht_cols", "k_dht_z_solve", "k_dhtx_update", "k_outer_resid_dhtx",
-                 "k_outer_update")
+SWEEP_KERNELS = ("k_resid_dhtx_z", "k_resid_dhtx_s", "k_dht_cols", "k_dht_cols_regs", "k_dht_z_solve",
+                 "k_dht_z_solve_regs", "k_dht_planes", "k_dhtx_update", "k_outer_resid_dhtx",
+                 "k_outer_resid_dhtx_s", "k_outer_update")
 
 
 def cmd_solves(a) -> None:
