@@ -502,13 +502,17 @@ __device__ __forceinline__ bool last_to_arrive(unsigned* counter, unsigned expec
     return true;
 }
 
-// Every thread of the block calls it once, after the block's last put_shared (by
-// thread 0) and its last read of the solve's state.  True in the last of the
-// gridDim.x blocks of the launch for this solve.
+// Every thread of the block calls it once, after its last put_shared and its last
+// read of the solve's state.  True in the last of the gridDim.x blocks of the launch
+// for this solve.  Once thread 0 has arrived, the last block may write the state, so
+// every wave of the block first waits until its own reads have returned and its
+// stores have reached memory, and thread 0 for all of them at the barrier (waves read
+// the state each for itself: one that comes late would see the next stage).
 __device__ __forceinline__ bool last_block(const Slot& s) {
     __shared__ int last;
+    asm volatile("s_waitcnt vmcnt(0) expcnt(0) lgkmcnt(0)" ::: "memory");
+    __syncthreads();
     if (threadIdx.x == 0) {
-        __builtin_amdgcn_s_waitcnt(0);  // this thread's stores have reached memory
         const unsigned nb = gridDim.x, group = blockIdx.x % kArriveGroups;
         const unsigned groups = nb < kArriveGroups ? nb : kArriveGroups;
         last = last_to_arrive(arrive_group(s.partial, group), (nb - group + kArriveGroups - 1) / kArriveGroups) &&
