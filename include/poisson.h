@@ -273,8 +273,8 @@ int poisson_project(poisson_t h, const double* rho, double* mx, double* my, doub
  * Deterministic (no floating-point atomics: the particles are sorted by cell,
  * and every cell adds its contributions in a fixed order, so repeated calls
  * give the same bits).  Keeps particle buffers in the handle, grown as needed
- * (80 B per particle); out must not overlap pos or q.  Blocks until
- * done. */
+ * (80 B per particle, and up to some MB by the grid); out must not overlap pos
+ * or q.  Blocks until done. */
 int poisson_deposit(poisson_t h, int n_particles, const double* pos, const double* q, double* out);
 
 /* out_p = I(field)(x_p): trilinear interpolation of a device FP64 cell field at

@@ -13,9 +13,10 @@
 // kPiece sorted particles (so a cell holding many particles costs a few piece
 // sums, not a long serial loop), and the pieces of a run are added in order into
 // its eight corner sums sum_p q_p W_a W_b W_e (a, b, e the offsets 0/1 of the
-// corner cell in x, y, z).  Then every block owns a few rows of the grid, adds
-// the corner sums that fall on them in LDS in a fixed order, and writes each of
-// its cells once (k_part_cells).  I is a plain gather, one thread per particle.
+// corner cell in x, y, z).  The runs are listed in the order of their cells.  Then
+// every block owns a few tiles of rows of the grid, adds the runs' corner sums that
+// fall on them in LDS in a fixed order, and writes each of its cells once
+// (k_part_cells).  I is a plain gather, one thread per particle.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -26,6 +27,7 @@
 namespace pois {
 
 constexpr int kPartThreads = 256;
+constexpr int kGroupStep = 32;  // words from one group's run count to the next
 
 // lower cell index and fraction of a coordinate along one direction; false if
 // the position is not finite or more than 2^30 cells away
@@ -67,8 +69,12 @@ k_part_keys(PartGeom pg, int np, const double* __restrict__ pos, uint2* __restri
     pair[p] = make_uint2(cell, (unsigned)p);
 }
 
-__global__ void __launch_bounds__(kPartThreads) k_part_flag_clear(int* __restrict__ bad) {
+// Clears the bad-position flag and the run counts of the groups (none for the
+// interpolation).
+__global__ void __launch_bounds__(kPartThreads)
+k_part_clear(int* __restrict__ bad, unsigned* __restrict__ group_runs, int groups) {
     if (threadIdx.x == 0) bad[0] = 0;
+    for (int q = threadIdx.x; q < groups; q += kPartThreads) group_runs[q * (size_t)kGroupStep] = 0u;
 }
 
 // ---- stable LSD radix sort of (key, index) pairs ----------------------------------
@@ -222,22 +228,40 @@ k_rs_scatter(int np, const uint2* __restrict__ pair, int shift, int db, const un
 // those at the following multiples of kPiece).
 constexpr int kPiece = 8;
 
+// The list of the runs, (cell, first position) in the order of the cells: the blocks
+// of k_part_pieces count the runs that start in their kPartThreads positions, for
+// themselves and for their group of blocks, and each block of k_part_runs adds the
+// counts before its own: of whole groups, and of blocks of its own group.  A group is
+// about the square root of the number of blocks, which keeps both short, and at least
+// 64; its counter has a cache line to itself (an atomic on a line takes some 10 ns:
+// 10^6 particles' 3907 blocks on four counters of one line cost 25 us, on 61 of four
+// lines 9).
+static int position_blocks(int np) { return (int)(((long long)np + kPartThreads - 1) / kPartThreads); }
+static int group_blocks(int np) {
+    int b = 64;
+    while ((long long)b * b < position_blocks(np)) b *= 2;
+    return b;
+}
+static int run_groups(int np) { return (position_blocks(np) + group_blocks(np) - 1) / group_blocks(np); }
+
 // The particles lie anywhere in memory: each thread gathers one (64 B, or two
 // lines of it), so that all of a block's loads are in flight together; then
 // eight threads sum each kPiece positions, one per corner, and store the eight
-// sums of a piece side by side.  (10^6 particles on 512^3: 47 us; one
+// sums of a piece side by side.  (10^6 particles on 512^3: 32 us; one
 // thread per kPiece particles and all corners took 64.)
 __global__ void __launch_bounds__(kPartThreads)
 k_part_pieces(PartGeom pg, int np, const double* __restrict__ pos, const double* __restrict__ q,
-              const uint2* __restrict__ pair, double* __restrict__ psum) {
+              const uint2* __restrict__ pair, double* __restrict__ psum, unsigned* __restrict__ block_runs,
+              unsigned* __restrict__ group_runs, int group_size) {
     static_assert(kPartThreads % kPiece == 0, "a block's positions start at a multiple of kPiece");
     __shared__ double f[4][kPartThreads];
-    __shared__ unsigned key[kPartThreads];
+    __shared__ unsigned key[kPartThreads], wave_runs[kPartThreads / 64];
     const int t = (int)threadIdx.x;
     const long long base = (long long)blockIdx.x * kPartThreads;
     const int n = (int)min((long long)kPartThreads, np - base);
+    const uint2 pr = pair[base + min(t, n - 1)];
+    const unsigned before = pair[max(base - 1, 0ll)].x;
     if (t < n) {
-        const uint2 pr = pair[base + t];
         const double* x = pos + 3 * (size_t)pr.y;
         int i;
         double fx = 0.0, fy = 0.0, fz = 0.0;
@@ -252,6 +276,9 @@ k_part_pieces(PartGeom pg, int np, const double* __restrict__ pos, const double*
         key[t] = pr.x;
     }
     __syncthreads();
+    const bool starts = t < n && ((t == 0 && base == 0) || (t > 0 ? key[t - 1] : before) != pr.x);
+    const unsigned long long started = __ballot(starts);
+    if ((t & 63) == 0) wave_runs[t >> 6] = (unsigned)__popcll(started);
     const int c = t & 7, p0 = (t >> 3) * kPiece, p1 = min(p0 + kPiece, n);
     double acc = 0.0;
     int at = p0;
@@ -265,17 +292,95 @@ k_part_pieces(PartGeom pg, int np, const double* __restrict__ pos, const double*
         acc += f[3][p] * ((c & 1) ? fx : 1.0 - fx) * ((c & 2) ? fy : 1.0 - fy) * ((c & 4) ? fz : 1.0 - fz);
     }
     if (p0 < n) psum[8 * (size_t)(base + at) + c] = acc;
+    __syncthreads();
+    if (t == 0) {
+        unsigned runs = 0u;
+#pragma unroll
+        for (int w = 0; w < kPartThreads / 64; ++w) runs += wave_runs[w];
+        block_runs[blockIdx.x] = runs;
+        atomicAdd(&group_runs[blockIdx.x / (unsigned)group_size * (size_t)kGroupStep], runs);  // integer: exact in any order
+    }
 }
 
-// (A run's later pieces are read kAhead at a time, so that one long run does not
+// The tiles of k_part_cells: `rows` rows of one plane, tiles_y of them per plane.
+// Where their rows begin in the list of runs is kept in 2 tiles_y edges per plane, in
+// the order of their rows: row 0; rows j0 - 1 and j0 of every later tile; row ny - 1
+// (the row below row 0).  After the last plane's comes the end of the list.
+struct TileGeom {
+    int nx, ny, rows, tiles_y;
+    unsigned tiles, group;  // all tiles, neighbouring tiles of a block
+    // edges up to and with the row of the cell
+    __host__ __device__ unsigned edges_to(unsigned cell) const {
+        const unsigned row = cell / (unsigned)nx, k = row / (unsigned)ny;
+        const int j = (int)(row - k * (unsigned)ny);
+        const int above = (j + 1) / rows;
+        return k * 2u * (unsigned)tiles_y + 1u + (unsigned)(above < tiles_y ? above : tiles_y - 1) +
+               (unsigned)(j / rows) + (j + 1 == ny ? 1u : 0u);
+    }
+    __host__ __device__ unsigned edges() const { return 2u * tiles; }
+};
+
+// edge[from, to) = value of every lane: by the lane where they are few, by the whole
+// wave, lane after lane, where they are many (few particles on a large grid).  Every
+// lane of the wave calls it.
+__device__ __forceinline__ void put_edges(int* __restrict__ edge, unsigned from, unsigned to, int value) {
+    constexpr unsigned kFew = 4;
+    const bool many = to - from > kFew;
+    if (!many)
+        for (unsigned e = from; e < to; ++e) edge[e] = value;
+    for (unsigned long long left = __ballot(many); left; left &= left - 1) {
+        const int src = __builtin_ctzll(left);
+        const unsigned f = (unsigned)__builtin_amdgcn_readlane((int)from, src);
+        const unsigned l = (unsigned)__builtin_amdgcn_readlane((int)to, src);
+        const int v = __builtin_amdgcn_readlane(value, src);
+        for (unsigned e = f + (threadIdx.x & 63u); e < l; e += 64u) edge[e] = v;
+    }
+}
+
+// No particles: every edge is the end of an empty list.
+__global__ void __launch_bounds__(kPartThreads) k_part_no_edges(unsigned n, int* __restrict__ edge) {
+    const unsigned e = blockIdx.x * kPartThreads + threadIdx.x;
+    if (e < n) edge[e] = 0;
+}
+
+// Adds the pieces of the runs that start in a block's positions, lists the runs and
+// puts the edges that lie between a run and the one before it, and after the last
+// run.  (A run's later pieces are read kAhead at a time, so that one long run does not
 // wait for memory at every piece.)
 __global__ void __launch_bounds__(kPartThreads)
-k_part_runs(int np, const uint2* __restrict__ pair, double* __restrict__ psum) {
+k_part_runs(int np, const uint2* __restrict__ pair, double* __restrict__ psum,
+            const unsigned* __restrict__ block_runs, const unsigned* __restrict__ group_runs, int group_size,
+            TileGeom tg, uint2* __restrict__ run, int* __restrict__ edge) {
     constexpr int kAhead = 4;
-    const long long s = (long long)blockIdx.x * kPartThreads + threadIdx.x;
-    if (s >= np) return;
-    const unsigned k = pair[s].x;
-    if (s > 0 && pair[s - 1].x == k) return;
+    __shared__ unsigned wave_first[kPartThreads / 64], wave_before[kPartThreads / 64];
+    const int t = (int)threadIdx.x, lane = t & 63, wave = t >> 6;
+    const long long s = (long long)blockIdx.x * kPartThreads + t;
+    const unsigned k = pair[min(s, (long long)np - 1)].x;
+    const unsigned prev = pair[min(max(s - 1, 0ll), (long long)np - 1)].x;
+    // runs that start before this block: whole groups, then the blocks of its own
+    const unsigned group = blockIdx.x / (unsigned)group_size;
+    unsigned before = 0u;
+    for (unsigned q = t; q < group; q += kPartThreads) before += group_runs[q * (size_t)kGroupStep];
+    for (unsigned b = group * (unsigned)group_size + t; b < blockIdx.x; b += kPartThreads) before += block_runs[b];
+    const bool starts = s < np && (s == 0 || prev != k);
+    const unsigned long long started = __ballot(starts);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o);
+    if (lane == 0) {
+        wave_before[wave] = before;
+        wave_first[wave] = (unsigned)__popcll(started);
+    }
+    __syncthreads();
+    unsigned at = 0u;
+#pragma unroll
+    for (int w = 0; w < kPartThreads / 64; ++w) at += wave_before[w] + (w < wave ? wave_first[w] : 0u);
+    at += (unsigned)__popcll(started & (lane == 0 ? 0ull : ~0ull >> (64 - lane)));
+    const unsigned here = tg.edges_to(k);
+    put_edges(edge, starts && s > 0 ? tg.edges_to(prev) : 0u, starts ? here : 0u, (int)at);
+    const bool last = s + 1 == np;
+    put_edges(edge, last ? here : 0u, last ? tg.edges() + 1u : 0u, (int)at + (starts ? 1 : 0));
+    if (!starts) return;
+    run[at] = make_uint2(k, (unsigned)s);
     long long nxt = (s / kPiece + 1) * kPiece;
     if (nxt >= np || pair[nxt].x != k) return;  // a single piece: its sums are the run's
     double acc[8];
@@ -286,10 +391,10 @@ k_part_runs(int np, const uint2* __restrict__ pair, double* __restrict__ psum) {
         double v[kAhead][8];
 #pragma unroll
         for (int u = 0; u < kAhead; ++u) {
-            const long long at = min(nxt + u * kPiece, (long long)np - 1);
-            kk[u] = pair[at].x;
+            const long long a = min(nxt + u * kPiece, (long long)np - 1);
+            kk[u] = pair[a].x;
 #pragma unroll
-            for (int c = 0; c < 8; ++c) v[u][c] = psum[8 * (size_t)at + c];
+            for (int c = 0; c < 8; ++c) v[u][c] = psum[8 * (size_t)a + c];
         }
 #pragma unroll
         for (int u = 0; u < kAhead; ++u) {
@@ -302,135 +407,131 @@ k_part_runs(int np, const uint2* __restrict__ pair, double* __restrict__ psum) {
     for (int c = 0; c < 8; ++c) psum[8 * (size_t)s + c] = acc[c];
 }
 
-// First sorted position with a key of at least `key`: a wave narrows the range
-// 64-fold per step (10^6 pairs: four dependent loads, where halving takes 20).
-__device__ __forceinline__ int first_at_least(const uint2* __restrict__ pair, int np, unsigned long long key) {
-    const long long lane = threadIdx.x & 63;
-    long long lo = 0, len = np;  // the answer is in [lo, lo + len]
-    while (len > 0) {
-        const long long step = (len + 63) / 64, at = lane * step;
-        const bool less = at < len && (unsigned long long)pair[lo + at].x < key;
-        const long long nless = __popcll(__ballot(less));
-        if (nless == 0) return (int)lo;
-        lo += (nless - 1) * step + 1;
-        len = min(step - 1, len - ((nless - 1) * step + 1));
-    }
-    return (int)lo;
-}
-
-// The same within [lo, hi], by one thread.
-__device__ __forceinline__ int first_between(const uint2* __restrict__ pair, int lo, int hi, unsigned long long key) {
-    while (lo < hi) {
-        const int mid = lo + (hi - lo) / 2;
-        if (pair[mid].x < key) lo = mid + 1;
-        else hi = mid;
-    }
-    return lo;
-}
-
-// The deposit itself: a block owns `span` tiles of `rows` rows of one plane, one
-// after the other, and gathers the corner sums that fall on each tile [j0, j1) x
-// nx in LDS.  They come from the runs of plane k - 1 (their upper half, e = 1) and
-// of plane k (e = 0), rows j0 - 1 to j1 - 1: two contiguous ranges of the sorted
-// pairs, and two more for the row below row 0, ny - 1.  Half of the block's
-// threads walk each plane's range.  Runs are distinct cells, so for one corner
-// (a, b) of one plane no two threads add to one cell; barriers separate the
-// corners, and every cell receives its contributions in the same order in every
-// call.  A run longer than a chunk of the walk is skipped by a search for its end.
+// The deposit itself: a block owns up to kSpanMax tiles of `rows` rows of one plane,
+// a few neighbours and then others far away, one after the other, and gathers the corner sums that fall on each
+// tile [j0, j1) x nx in LDS.  They come from the runs of plane k - 1 (their upper half,
+// e = 1) and of plane k (e = 0), rows j0 - 1 to j1 - 1: two contiguous ranges of the
+// list of runs, and two more for the row below row 0, ny - 1.  Half of the block's
+// threads take each plane's range, kRuns runs each at a time.  Runs are distinct cells,
+// so for one corner (a, b) of one plane no two threads add to one cell; barriers
+// separate the corners, and every cell receives its contributions in the same order
+// in every call.
 //
-// What bounds it is the grid's one write, and, per tile, the chain bounds - pairs
-// - sums - LDS: the bounds of all the block's tiles are found at once (one tile
-// per block and the planes in turn: 381 us for 10^6 particles on 512^3).  Filling
-// the grid with zeros and adding the runs in eight passes (one per parity class
-// of the run's cell) moved whole lines both ways for 8-byte updates: 172 us of
-// filling beside the sort and 267 us of passes after it, now 255 us in all (4.2
-// TB/s of the grid's 1.07 GB).  Deposits, before and after: 10^6 particles on
-// 512^3 746 -> 416 us (10^4 of them in one cell 1264 -> 634, all of them 53.5 ->
-// 22.1 ms), 2 10^6 on 256^3 647 -> 310, 2000 on 32^3 160 -> 80.
-constexpr int kSpanMax = 32;  // tiles of a block at most (their bounds: 512 bytes of LDS)
+// What bounds it is the grid's one write, and, per tile, the chain runs - sums -
+// LDS.  Filling the grid with zeros and adding the runs in eight passes (one per
+// parity class of the run's cell) moved whole lines both ways for 8-byte updates:
+// 172 us of filling beside the sort and 267 us of passes after it, for 10^6 particles
+// on 512^3, now 265 us in all (4.1 TB/s of the grid's 1.07 GB).
+// A tile's work is bounded by its cells, however many particles they hold, because
+// it walks runs, and particles that crowd some planes or rows crowd tiles of many
+// blocks, because most of a block's tiles lie far apart.  (Walking the particles, in
+// tiles that were all neighbours, was 7 us faster on uniform particles and took 3870
+// us for 10^6 of them in one plane of 512^3, 6850 in 16 rows of it.)  Deposits, passes
+// by class / now, us: 10^6 on 512^3 uniform 732 / 432, one plane 490 / 470, 16 rows 500 /
+// 430, a ball of 16^3 cells 490 / 398, one cell 53500 / 22100; 2 10^6 on 256^3 639 / 306,
+// 2000 on 32^3 152 / 75.
+constexpr unsigned kSpanMax = 32;  // tiles of a block at most: one thread per bound (of eight)
+// runs of a thread at a time (10^6 uniform particles on 64 x 512 x 512, x first: 213 us;
+// with four 235)
+constexpr int kRuns = 2;
+
+// Tile m of block b of nb, whose groups are `group` tiles.
+__host__ __device__ __forceinline__ unsigned block_tile(unsigned m, unsigned group, unsigned b, unsigned nb) {
+    const unsigned g = m / group;
+    return (g * nb + b) * group + (m - g * group);
+}
 
 __global__ void __launch_bounds__(kPartThreads)
-k_part_cells(PartGeom pg, int np, const uint2* __restrict__ pair, const double* __restrict__ psum,
-             const int* __restrict__ bad, int rows, int span, int spans, double* __restrict__ out) {
+k_part_cells(PartGeom pg, TileGeom tg, const uint2* __restrict__ run, const int* __restrict__ edge,
+             const double* __restrict__ psum, const int* __restrict__ bad, double* __restrict__ out) {
     constexpr int kHalf = kPartThreads / 2;
+    static_assert(8 * kSpanMax == kPartThreads, "one thread per bound");
     extern __shared__ double acc[];
-    __shared__ int edge[2][2], wrap_edge[2][2];   // [plane k - 1, k][first, end]: the block's rows; row ny - 1
-    __shared__ int bound[kSpanMax][2][2];
-    if (bad[0]) return;  // a bad position: the output stays as it is
-    const int nx = pg.nx, ny = pg.ny, nz = pg.nz, t = (int)threadIdx.x;
-    const int k = (int)(blockIdx.x / (unsigned)spans);
-    const int jb0 = (int)(blockIdx.x - (unsigned)k * (unsigned)spans) * rows * span, jb1 = min(jb0 + rows * span, ny);
-    const int tiles = (jb1 - jb0 + rows - 1) / rows;
-    const unsigned row0[2] = {(unsigned)(k == 0 ? nz - 1 : k - 1) * (unsigned)ny, (unsigned)k * (unsigned)ny};
-    const auto row_key = [&](int pl, int row) {
-        return (unsigned long long)(row0[pl] + (unsigned)row) * (unsigned)nx;
-    };
-    {
-        const int w = __builtin_amdgcn_readfirstlane(t >> 6), pl = w >> 1, end = w & 1;
-        const int a = first_at_least(pair, np, row_key(pl, end ? jb1 : max(jb0 - 1, 0)));
-        const int b = jb0 == 0 ? first_at_least(pair, np, row_key(pl, ny - 1 + end)) : 0;
-        if ((t & 63) == 0) {
-            edge[pl][end] = a;
-            wrap_edge[pl][end] = b;
-        }
+    __shared__ int bound[kSpanMax][2][4];  // [tile][plane k - 1, k]: its rows' first run and end; row ny - 1's
+    const int nx = pg.nx, ny = pg.ny, nz = pg.nz, rows = tg.rows, t = (int)threadIdx.x;
+    const unsigned tiles_y = (unsigned)tg.tiles_y, tiles = tg.tiles;
+    const int flag = bad[0];
+    if (const unsigned tile = block_tile((unsigned)t >> 3, tg.group, blockIdx.x, gridDim.x); tile < tiles) {
+        const unsigned k = tile / tiles_y, jt = tile - k * tiles_y;
+        const unsigned kp = (t & 4) ? k : k == 0 ? (unsigned)nz - 1 : k - 1;
+        const int which = t & 3;  // row max(j0 - 1, 0); row j1; row ny - 1; the plane's end
+        const unsigned e = which == 0 ? (jt == 0 ? 0u : 2 * jt - 1)
+                           : which == 1 ? 2 * jt + 2
+                                        : 2 * tiles_y - (which == 2 ? 1u : 0u);
+        bound[t >> 3][(t >> 2) & 1][which] = edge[kp * 2 * tiles_y + e];
     }
+    if (flag) return;  // a bad position: the output stays as it is
     __syncthreads();
-    for (int q = t; q < 4 * tiles; q += kPartThreads) {
-        const int m = q >> 2, pl = (q >> 1) & 1, end = q & 1, j0 = jb0 + m * rows;
-        int at;
-        if (end == 0 && m == 0) at = edge[pl][0];
-        else if (end == 1 && m == tiles - 1) at = edge[pl][1];
-        else at = first_between(pair, edge[pl][0], edge[pl][1], row_key(pl, end ? j0 + rows : j0 - 1));
-        bound[m][pl][end] = at;
-    }
-    const int pl = t / kHalf;  // the plane this thread walks
-    for (int m = 0; m < tiles; ++m) {
-        const int j0 = jb0 + m * rows, j1 = min(j0 + rows, ny), cells = (j1 - j0) * nx;
+    const int pl = __builtin_amdgcn_readfirstlane(t / kHalf);  // the plane whose runs this wave takes
+    const int wave0 = __builtin_amdgcn_readfirstlane(t & (kHalf - 64)), lane = t & 63;
+    for (unsigned m = 0; m < kSpanMax; ++m) {
+        const unsigned tile = block_tile(m, tg.group, blockIdx.x, gridDim.x);
+        if (tile >= tiles) break;
+        const int k = (int)(tile / tiles_y), j0 = (int)(tile - (unsigned)k * tiles_y) * rows;
+        const int j1 = min(j0 + rows, ny), cells = (j1 - j0) * nx;
+        const unsigned row0 = (unsigned)(pl ? k : k == 0 ? nz - 1 : k - 1) * (unsigned)ny;
         for (int c = t; c < cells; c += kPartThreads) acc[c] = 0.0;
         __syncthreads();
         for (int wrap = j0 == 0 ? 1 : 0; wrap >= 0; --wrap) {
-            long long at[2], hi[2];
+            int lo[2], hi[2];
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
-                at[u] = wrap ? wrap_edge[u][0] : bound[m][u][0];
-                hi[u] = wrap ? wrap_edge[u][1] : bound[m][u][1];
+                lo[u] = __builtin_amdgcn_readfirstlane(bound[m][u][2 * wrap]);
+                hi[u] = __builtin_amdgcn_readfirstlane(bound[m][u][2 * wrap + 1]);
             }
-            while (at[0] < hi[0] || at[1] < hi[1]) {
-                const long long s = (pl ? at[1] : at[0]) + (t & (kHalf - 1));
-                double w[4] = {0.0, 0.0, 0.0, 0.0};
-                int c0 = -1, c1 = -1, dx = 0;
-                if (s < (pl ? hi[1] : hi[0])) {
-                    const unsigned key = pair[s].x;
-                    if (s == 0 || pair[s - 1].x != key) {
+            const int most = max(hi[0] - lo[0], hi[1] - lo[1]), end = pl ? hi[1] : hi[0];
+            const auto add = [&]<int R>(int first) {
+                // all the runs' loads, then all their sums', then the cells: lanes past
+                // the end take the last run and add nothing
+                const int at0 = (pl ? lo[1] : lo[0]) + first + wave0;
+                uint2 rn[R];
+                double w[R][4];
 #pragma unroll
-                        for (int q = 0; q < 4; ++q) w[q] = psum[8 * (size_t)s + (pl ? 0 : 4) + q] * pg.inv_v;
-                        const unsigned row = key / (unsigned)nx;
-                        const int i = (int)(key - row * (unsigned)nx), j = (int)(row - (pl ? row0[1] : row0[0]));
-                        dx = i + 1 == nx ? -i : 1;
-                        if (!wrap && j >= j0) c0 = (j - j0) * nx + i;
-                        if (wrap) c1 = i;
-                        else if (j + 1 < j1) c1 = (j + 1 - j0) * nx + i;
+                for (int r = 0; r < R; ++r)
+                    if (at0 + r * kHalf < end) rn[r] = run[min(at0 + r * kHalf + lane, end - 1)];
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+                    if (at0 + r * kHalf < end) {
+                        const double* sums = psum + 8 * (size_t)rn[r].y + (pl ? 0 : 4);
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) w[r][q] = sums[q];
+                    }
+                int c0[R], c1[R], dx[R];
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    c0[r] = c1[r] = -1;
+                    if (at0 + r * kHalf < end) {
+                        const unsigned row = rn[r].x / (unsigned)nx;
+                        const int i = (int)(rn[r].x - row * (unsigned)nx), j = (int)(row - row0);
+                        const bool in = at0 + r * kHalf + lane < end;
+                        dx[r] = i + 1 == nx ? -i : 1;
+                        if (in && !wrap && j >= j0) c0[r] = (j - j0) * nx + i;
+                        if (in && wrap) c1[r] = i;
+                        else if (in && j + 1 < j1) c1[r] = (j + 1 - j0) * nx + i;
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) w[r][q] *= pg.inv_v;
                     }
                 }
 #pragma unroll
                 for (int u = 0; u < 2; ++u) {
-                    if (at[u] >= hi[u]) continue;
+                    if (lo[u] + first >= hi[u]) continue;  // the same in every thread
                     const bool mine = pl == u;
-                    if (mine && c0 >= 0) acc[c0] += w[0];
-                    __syncthreads();
-                    if (mine && c0 >= 0) acc[c0 + dx] += w[1];
-                    __syncthreads();
-                    if (mine && c1 >= 0) acc[c1] += w[2];
-                    __syncthreads();
-                    if (mine && c1 >= 0) acc[c1 + dx] += w[3];
-                    __syncthreads();
-                    at[u] += kHalf;
-                    if (at[u] < hi[u]) {
-                        const unsigned last = pair[at[u] - 1].x;
-                        if (pair[min(at[u] + kHalf, hi[u]) - 1].x == last)
-                            at[u] = first_at_least(pair, np, (unsigned long long)last + 1u);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+#pragma unroll
+                        for (int r = 0; r < R; ++r)
+                            if (mine && at0 + r * kHalf < end) {
+                                const int c = q < 2 ? c0[r] : c1[r];
+                                if (c >= 0) acc[c + ((q & 1) ? dx[r] : 0)] += w[r][q];
+                            }
+                        __syncthreads();
                     }
                 }
+            };
+            if (most <= kHalf) {
+                if (most > 0) add.template operator()<1>(0);
+            } else {
+                for (int first = 0; first < most; first += kRuns * kHalf) add.template operator()<kRuns>(first);
             }
         }
         // (a thread writes and clears the same cells of LDS: no barrier between the two)
@@ -439,23 +540,32 @@ k_part_cells(PartGeom pg, int np, const uint2* __restrict__ pair, const double* 
     }
 }
 
-// Rows of a tile of k_part_cells: eight, or what fits 32 KB of LDS (five blocks per
-// CU), fewer where that leaves the chip without four blocks per CU.  More rows
-// share the search and the row below the tile (10^6 particles on 512^3: 491, 433
-// and 416 us with 2, 4 and 8 rows; 3 10^5 on 384 x 192 x 768: 240 with 2, 221 with
-// 5), more than eight leave too little work in flight (2 10^6 on 256^3: 317 with 8,
-// 334 with 16).  Then as many tiles per block as leave eight blocks per CU (fewer
-// would not fill it, more repeat the search for the rows' bounds: with 32 blocks
-// per CU 460 us on 512^3 and 337 on 256^3 where it was 444 and 317).
+// Rows of a tile of k_part_cells: eight, or what fits 32 KB of LDS (four blocks per
+// CU), fewer where that leaves the chip without four blocks per CU.  More rows share
+// the row below the tile (10^6 particles on 512^3: 510, 432 and 436 us with 2, 4 and 8
+// rows; on 64 x 512 x 512, x first: 350, 270 and 220; 3 10^5 on 768 x 192 x 384: 221 with
+// 2 and 205 with 5).  Then as many tiles per block as leave eight blocks per CU.
 static int tile_rows(const GridArgs& g) {
     int rows = std::max(1, std::min({g.ny, 8, 4096 / g.nx}));
     while (rows > 1 && (long long)g.nz * ((g.ny + rows - 1) / rows) < 1024) rows = (rows + 1) / 2;
     return rows;
 }
 
-static int tile_span(const GridArgs& g, int rows) {
-    const int tiles = (g.ny + rows - 1) / rows;
-    return std::max(1, std::min({tiles, kSpanMax, (int)((long long)tiles * g.nz / 2048)}));
+// Neighbouring tiles of a block, up to kTileGroup of them: neighbours are written a
+// little faster, tiles far apart share out a crowd (10^6 particles on 512^3, uniform /
+// in one plane: 1 of 16 tiles 444 / 443 us, 2 432 / 469, 4 431 / 525, 8 437 / 686).
+constexpr unsigned kTileGroup = 2;
+
+static TileGeom tile_geom(const GridArgs& g) {
+    const int rows = tile_rows(g), tiles_y = (g.ny + rows - 1) / rows;
+    const unsigned tiles = (unsigned)g.nz * (unsigned)tiles_y;
+    return TileGeom{g.nx, g.ny, rows, tiles_y, tiles, std::clamp(tiles / 2048u, 1u, kTileGroup)};
+}
+
+static unsigned tile_blocks(const TileGeom& tg) {
+    const unsigned groups = (tg.tiles + tg.group - 1) / tg.group;
+    const unsigned span = std::clamp(groups / 2048u, 1u, kSpanMax / kTileGroup);
+    return (groups + span - 1) / span;
 }
 
 __global__ void __launch_bounds__(kPartThreads)
@@ -511,14 +621,15 @@ static size_t up256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 static int sort_tiles(int np) { return (int)(((long long)np + kSortTile - 1) / kSortTile); }
 
-// The pairs (two copies for the sort passes), the piece and run sums, the digit
-// totals, the bad-position flag.  The (tile, digit) counts of the sort lie where
-// the sums come later.
+// The pairs (two copies for the sort passes; the list of runs takes the one that the
+// last pass leaves), the piece and run sums, the digit totals, the run counts, the
+// tiles' edges, the bad-position flag.  The (tile, digit) counts of the sort
+// lie where the sums come later.
 size_t particle_workspace_bytes(const GridArgs& g, int np) {
-    (void)g;
     return 2 * up256((size_t)np * 8) +
            std::max(up256((size_t)np * 64), up256((size_t)kDigits * std::max(1, sort_tiles(np)) * 4)) +
-           up256((size_t)kDigits * 4) + 256;
+           up256((size_t)kDigits * 4) + up256((size_t)position_blocks(np) * 4) + up256((size_t)run_groups(np) * kGroupStep * 4) +
+           up256(((size_t)tile_geom(g).edges() + 1) * 4) + 256;
 }
 
 hipError_t launch_deposit(const GridArgs& g, int np, const double* pos, const double* q, double* out, void* ws,
@@ -530,14 +641,21 @@ hipError_t launch_deposit(const GridArgs& g, int np, const double* pos, const do
     int* bad = reinterpret_cast<int*>(w);
     unsigned* digit_tot = reinterpret_cast<unsigned*>(w + 256);
     w += 256 + up256((size_t)kDigits * 4);
+    unsigned* block_runs = reinterpret_cast<unsigned*>(w);
+    w += up256((size_t)position_blocks(np) * 4);
+    unsigned* group_runs = reinterpret_cast<unsigned*>(w);
+    w += up256((size_t)run_groups(np) * kGroupStep * 4);
+    const TileGeom tg = tile_geom(g);
+    int* edge = reinterpret_cast<int*>(w);
+    w += up256(((size_t)tg.edges() + 1) * 4);
     uint2* pair = reinterpret_cast<uint2*>(w);
     uint2* pair2 = reinterpret_cast<uint2*>(w + kb);
     double* psum = reinterpret_cast<double*>(w + 2 * kb);
     unsigned* counts = reinterpret_cast<unsigned*>(psum);
     hipError_t e;
-    k_part_flag_clear<<<1, 64, 0, s>>>(bad);
+    k_part_clear<<<1, kPartThreads, 0, s>>>(bad, group_runs, run_groups(np));
     if (np > 0) {
-        const unsigned pb = ((unsigned)np + kPartThreads - 1) / kPartThreads;
+        const unsigned pb = (unsigned)position_blocks(np);
         k_part_keys<<<pb, kPartThreads, 0, s>>>(pg, np, pos, pair, bad);
         const int tiles = sort_tiles(np), bits = key_bits(g.n);
         const int passes = (bits + kDigitBits - 1) / kDigitBits;
@@ -550,12 +668,15 @@ hipError_t launch_deposit(const GridArgs& g, int np, const double* pos, const do
             if ((e = hipGetLastError()) != hipSuccess) return e;
             std::swap(pair, pair2);
         }
-        k_part_pieces<<<pb, kPartThreads, 0, s>>>(pg, np, pos, q, pair, psum);
-        k_part_runs<<<pb, kPartThreads, 0, s>>>(np, pair, psum);
+        k_part_pieces<<<pb, kPartThreads, 0, s>>>(pg, np, pos, q, pair, psum, block_runs, group_runs,
+                                                       group_blocks(np));
+        k_part_runs<<<pb, kPartThreads, 0, s>>>(np, pair, psum, block_runs, group_runs, group_blocks(np), tg,
+                                                     pair2, edge);
+    } else {
+        k_part_no_edges<<<(tg.edges() + kPartThreads) / kPartThreads, kPartThreads, 0, s>>>(tg.edges() + 1, edge);
     }
-    const int rows = tile_rows(g), span = tile_span(g, rows), spans = (g.ny + rows * span - 1) / (rows * span);
-    k_part_cells<<<(unsigned)g.nz * (unsigned)spans, kPartThreads, (size_t)rows * g.nx * sizeof(double), s>>>(
-        pg, np, pair, psum, bad, rows, span, spans, out);
+    k_part_cells<<<tile_blocks(tg), kPartThreads, (size_t)tg.rows * g.nx * sizeof(double), s>>>(
+        pg, tg, pair2, edge, psum, bad, out);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     int flag = 0;
     if ((e = hipMemcpyAsync(&flag, bad, sizeof(int), hipMemcpyDeviceToHost, s)) != hipSuccess) return e;
@@ -567,7 +688,7 @@ hipError_t launch_deposit(const GridArgs& g, int np, const double* pos, const do
 hipError_t launch_interpolate(const GridArgs& g, int np, const double* pos, const double* field, double* out,
                               int* bad_dev, int* bad_host, hipStream_t s) {
     const PartGeom pg = part_geom(g);
-    k_part_flag_clear<<<1, 64, 0, s>>>(bad_dev);
+    k_part_clear<<<1, kPartThreads, 0, s>>>(bad_dev, nullptr, 0);
     if (np > 0) k_part_interp<<<(np + kPartThreads - 1) / kPartThreads, kPartThreads, 0, s>>>(pg, np, pos, field,
                                                                                                out, bad_dev);
     hipError_t e = hipGetLastError();
