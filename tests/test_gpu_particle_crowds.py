@@ -94,3 +94,29 @@ def test_a_crowd_costs_no_multiple_of_a_uniform_deposit(box):
     crowd = 0.4 + uniform * torch.tensor(box, dtype=torch.float64, device="cuda")
     _times(shape, uniform, 3)
     assert _times(shape, crowd) <= 2.5 * _times(shape, uniform)
+
+
+def test_a_refused_deposit_is_quick():
+    # every position bad: all get one key, whose one run is not to be summed before
+    # the deposit is refused (it took 70 times a good deposit's time)
+    import torch
+
+    announce("deposit: all positions bad")
+    shape, n = (256, 256, 256), 10**6
+    good = torch.rand((n, 3), dtype=torch.float64, device="cuda")
+    bad = torch.full((n, 3), float("nan"), dtype=torch.float64, device="cuda")
+    h = P.poisson_create(shape, (1.0, 1.0, 1.0))
+    out = torch.full(shape, 7.0, dtype=torch.float64, device="cuda")
+    ts = []
+    try:
+        for _ in range(5):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            with pytest.raises(P.PoissonError) as e:
+                P.poisson_deposit(h, bad, None, out)
+            ts.append(time.perf_counter() - t)
+            assert e.value.code == P.POISSON_EDOMAIN
+        assert bool((out == 7.0).all())
+    finally:
+        P.poisson_destroy(h)
+    assert sorted(ts)[2] <= 2.0 * _times(shape, good)
