@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "poisson_control.hpp"
 #include "poisson_device.hpp"
@@ -139,6 +140,12 @@ k_resid_dhtx(GridArgs g, const Slot* __restrict__ slots, Tables tb, int decide) 
     if (MODE == 0) p1_decide<T, C::NT>(g, s, ngroups, decide, red);
 }
 
+// In what an FP32 residual is squared and added up, over a flush, for the norms of the
+// inner stopping test: FP32 on rows of whole waves, FP64 on the others (16 to 96
+// cells, where it costs nothing that was measured: 96^3 632 us a solve with either).
+template <int N>
+using NormSum = std::conditional_t<N % 64 == 0, float, double>;
+
 // P1 on rows of 16 and more: the residual of a tile of `nflush` KF planes x
 // SUB row pairs is computed by z-marching columns (see ZMarch); every KF
 // planes the tile's lines are transformed along x and written out.
@@ -210,7 +217,7 @@ k_resid_dhtx_z(GridArgs g, const Slot* __restrict__ slots, Tables tb, int nflush
         constexpr bool kZC = COEF == 0 && Z::CPT == 1;
         T zc[Z::CPT][2];
         for (int f = 0; f < nflush && k0 + f * KF < (int)nz; ++f) {
-            T tacc[2] = {T(0), T(0)};
+            NormSum<N> tacc[2] = {0, 0};
             // fully unrolled, so that the rotation of the plane registers below
             // is a renaming and not a copy that would wait for the prefetched loads
 #pragma unroll
@@ -257,9 +264,10 @@ k_resid_dhtx_z(GridArgs g, const Slot* __restrict__ slots, Tables tb, int nflush
                             acc[3] += o.a.pc * o.a.pc + o.b.pc * o.b.pc;
                         } else {
                             // FP32 inner sweeps: only the two norms are used (the
-                            // stopping test), summed in FP32 over the flush
-                            tacc[0] += o.a.r * o.a.r + o.b.r * o.b.r;
-                            tacc[1] += o.a.bt * o.a.bt + o.b.bt * o.b.bt;
+                            // stopping test)
+                            using S = NormSum<N>;
+                            tacc[0] += (S)o.a.r * o.a.r + (S)o.b.r * o.b.r;
+                            tacc[1] += (S)o.a.bt * o.a.bt + (S)o.b.bt * o.b.bt;
                         }
                     }
                     lds[(q * Z::SUB + sidx) * LF::LS + LF::pos((int)x_slot(i, N, BCX))] = qv;
@@ -347,7 +355,8 @@ k_resid_dhtx_s(GridArgs g, const Slot* __restrict__ slots, Tables tb, int decide
         for (int q = 0; q < KF; ++q)
             zm.template x_put<Z::DPP>(xb + (q * Z::SUB + sidx) * Z::XV, i, pl[q + 1]);
         __syncthreads();
-        T zc[2], tacc[2] = {T(0), T(0)};
+        T zc[2];
+        NormSum<N> tacc[2] = {0, 0};
 #pragma unroll
         for (int q = 0; q < KF; ++q) {
             const bool valid = jvalid && k0 + q < (int)nz;
@@ -368,8 +377,9 @@ k_resid_dhtx_s(GridArgs g, const Slot* __restrict__ slots, Tables tb, int decide
                     acc[2] += o.a.pc + o.b.pc;
                     acc[3] += o.a.pc * o.a.pc + o.b.pc * o.b.pc;
                 } else {
-                    tacc[0] += o.a.r * o.a.r + o.b.r * o.b.r;
-                    tacc[1] += o.a.bt * o.a.bt + o.b.bt * o.b.bt;
+                    using S = NormSum<N>;
+                    tacc[0] += (S)o.a.r * o.a.r + (S)o.b.r * o.b.r;
+                    tacc[1] += (S)o.a.bt * o.a.bt + (S)o.b.bt * o.b.bt;
                 }
             }
             lds[(q * Z::SUB + sidx) * LF::LS + LF::pos((int)x_slot(i, N, g.bcx))] = qv;
