@@ -1,6 +1,7 @@
 """A solve takes the fused y, z and y sweeps alone and the single ones in a batch
 where the batch makes the launch too large: the same bits, also where the single
-sweeps run their wide line groups (32768 lines of 16)."""
+sweeps run their wide line groups (32768 lines of 16).  And the fused launch where
+it has fewer blocks than columns, so that a block takes several."""
 import numpy as np
 import pytest
 
@@ -38,3 +39,27 @@ def test_fused_and_single_sweeps_same_bits(shape, precision, bc):
     assert np.abs(outs[0]).max() > 0.0
     assert np.array_equal(outs[0], outs[1])
     assert np.array_equal(outs[0], outs[2])
+
+
+@pytest.mark.parametrize("precision", [P.POISSON_FP64, P.POISSON_FP32_REFINE])
+def test_a_block_takes_several_columns(precision):
+    # 512 columns beside requests 64 times smaller: the large request's sweeps get one
+    # block on each of half the CUs
+    from paper_1601_05448_amd import serve
+
+    announce("planes: several columns per block", precision)
+    shapes = [(16, 16, 1024)] + [(16, 16, 16)] * 6
+    probs = [_problem(sh, 900 + k) for k, sh in enumerate(shapes)]
+    alone, jobs = [], []
+    for k, (sh, (rho, b)) in enumerate(zip(shapes, probs)):
+        with P.Solver(sh, (1.0, 1.0, 1.0), precision=precision) as s:
+            p = dev(np.zeros(sh))
+            assert s.solve(rho, b, p, 1e-9)["code"] == P.POISSON_OK
+            alone.append(host(p))
+        jobs.append(serve.Job(arrival_s=0.0, shape=sh, lengths=(1.0, 1.0, 1.0), rho=rho, b=b, p=dev(np.zeros(sh)), tol=1e-9,
+                              tag=k))
+    with serve.Server(1 << 30, 16, precision=precision) as s:
+        res = serve.replay(s, jobs, realtime=False)
+    assert len(res.outcomes) == len(jobs)
+    for o in res.outcomes:
+        assert np.array_equal(host(o.job.p), alone[o.job.tag]), o.job.tag
