@@ -212,10 +212,6 @@ template <typename T>
 __device__ __forceinline__ cpx<T> scaled_conj_h(cpx<T> zk, cpx<T> zm, T hp, T hm) {
     return {hp * zk.x + hm * zm.x, hm * zm.y - hp * zk.y};  // conj(hp Z_k + hm conj Z_{N-k})
 }
-template <typename T>
-__device__ __forceinline__ cpx<T> scaled_conj(cpx<T> zk, cpx<T> zm, T sa, T sb) {
-    return scaled_conj_h(zk, zm, T(0.5) * (sa + sb), T(0.5) * (sa - sb));
-}
 
 // The register paths take hp = (s_a + s_b)/2 and hm = (s_a - s_b)/2 with one
 // reciprocal per wavenumber instead of two.  The symbols are scaled by a power

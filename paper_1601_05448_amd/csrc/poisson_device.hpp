@@ -690,13 +690,6 @@ __device__ __forceinline__ cpx<T> x_forward_out(const cpx<T>* line, int k, int b
     return bcx ? dct_out(zk, zm, twc[k]) : hartley(zk, zm);
 }
 
-// 1 / (n (lx + ly + lz)), 0 for the constant mode (the zero-mean gauge)
-template <typename T>
-__device__ __forceinline__ T inv_symbol(T lx, T ly, T lz, T n) {
-    const T lam = lx + ly + lz;
-    return lam == T(0) ? T(0) : recip(n * lam);
-}
-
 // Calls f.template operator()<N>() for the runtime length n.
 template <typename F>
 inline hipError_t dispatch_len(int n, F&& f) {

@@ -255,8 +255,6 @@ k_outer_resid_dhtx_s(GridArgs g, const Slot* __restrict__ slots, Tables tb, int 
 
 bool outer_fusable(const GridArgs& g) { return g.nx >= 16; }
 
-constexpr int kSmallPlanes = 2;  // of a small tile
-
 hipError_t launch_outer_fused(const GridArgs& g, const Tables& t, const Slot* slots, int nslots, hipStream_t s,
                               float share, bool write, bool decide) {
     const int wr = write ? 1 : 0, dec = decide ? 1 : 0;

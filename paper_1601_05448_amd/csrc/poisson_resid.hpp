@@ -413,9 +413,6 @@ static hipError_t run_gather(const GridArgs& g, const Tables& t, const Slot* slo
     return hipGetLastError();
 }
 
-// Planes of a small tile.
-constexpr int kSmallPlanes = 2;
-
 template <typename T, int N, int CO, int WE>
 static hipError_t run_small(const GridArgs& g, const Tables& t, const Slot* slots, int nslots, hipStream_t s,
                             float share, int decide, bool* fits) {

@@ -90,6 +90,9 @@ inline int pick_flushes(int kf, int most, unsigned strips, unsigned nz, unsigned
     return best;
 }
 
+// Planes of a small tile.
+constexpr int kSmallPlanes = 2;
+
 // Whether a sweep takes its small tiles (all loads at once): where they all fit on
 // the chip at once, so that the sweep lasts one block's chain (64^3 in FP64: 6.7 us,
 // marching 11.0; 96^3, more than one round: 17.5 against 12.6).
