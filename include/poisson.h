@@ -184,8 +184,11 @@ int poisson_residual(poisson_t h, const double* rho, const double* b, const doub
  * bracketed by two HIP events on the handle's stream (up to 256 launches per
  * solve) and the elapsed times are summed when the solve returns; launches
  * that find their solve finished or out of stage are counted too (compare
- * poisson_stats.p1_sweeps).  sweep 0 stops the timer.  Every call resets the
- * sums. */
+ * poisson_stats.p1_sweeps).  Small grids (16 to 64 cells along y and z, at most
+ * 2304 in a y-z plane and 589824 complex values in all) run sweeps 2, 3 and 2 as
+ * one launch, which has no sweep number: while sweep 2 or 3 of such a grid is
+ * timed, its solves run the three one by one, with the same results.  sweep 0
+ * stops the timer.  Every call resets the sums. */
 int poisson_kernel_timer(poisson_t h, int sweep, int fp32);
 /* Summed bracketed time (ms) and bracketed launches since the timer was set. */
 int poisson_kernel_timer_read(poisson_t h, double* total_ms, long long* launches);
@@ -208,8 +211,10 @@ int poisson_lap_pinv_fp32(poisson_t h, const double* q, double* delta);
 /* Average device time of one sweep of the iteration, launched `reps` times
  * back to back between two HIP events on the handle's stream (after one
  * warm-up launch), written to *avg_ms.  sweep: 1 residual + weight + Hartley
- * along x; 2 Hartley along y; 3 Hartley along z, symbol division, Hartley
- * along z; 5 Hartley along x + update; 6 (POISSON_FP32_REFINE handles only)
+ * along x, without the decision that ends it in a solve; 2 Hartley along y; 3
+ * Hartley along z, symbol division, Hartley along z (2 and 3 as single launches
+ * also on the small grids whose solves run them as one, see
+ * poisson_kernel_timer); 5 Hartley along x + update; 6 (POISSON_FP32_REFINE handles only)
  * the FP64 outer residual of a refinement step with its FP32 outputs (where
  * the rows allow it, fused with the first inner sweep's residual and its
  * transform along x).

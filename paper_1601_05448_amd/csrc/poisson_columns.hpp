@@ -32,8 +32,9 @@ __device__ __forceinline__ unsigned col_base(const GridArgs& g, unsigned line) {
 //
 // Lines per block of the column sweeps on FftPlan lines.  Wide: about 256
 // threads and runs of at least 128 bytes per row (8 FP64 or 16 FP32 complex
-// values; 8 on FP32 lines of 768 and 1024, whose 1024-thread blocks would spill).  Narrow: one to four waves, for grids whose wide line groups would
-// not give every CU two blocks (kWideGroups): such sweeps are bound by the
+// values; 8 on FP32 lines of 768 and 1024, whose 1024-thread blocks would spill).
+// Narrow: one to four waves, for grids whose wide line groups would not give every CU
+// two blocks (kWideGroups): such sweeps are bound by the
 // latency of one block's chain of loads, transposes and stores, and more, smaller
 // blocks spread the same lines over more CUs.
 template <typename T, int N>

@@ -420,7 +420,7 @@ static hipError_t five_sweeps(const GridArgs& g, const Tables& t, const Slot* sl
     };
     if ((parts & 1) && (e = sweep(1)) != hipSuccess) return e;
     if (!(parts & 2)) return hipSuccess;
-    // a timed y or z sweep runs by itself
+    // a timed y or z sweep runs by itself (poisson_kernel_timer)
     if (planes_fusable(g, nslots) && !(tm && tm->fp32 == fp32 && (tm->sweep == 2 || tm->sweep == 3))) {
         if ((e = sweep(kSweepPlanes)) != hipSuccess) return e;
         return sweep(5);

@@ -149,12 +149,15 @@ using NormSum = std::conditional_t<N % 64 == 0, float, double>;
 // P1 on rows of 16 and more: the residual of a tile of `nflush` KF planes x
 // SUB row pairs is computed by z-marching columns (see ZMarch); every KF
 // planes the tile's lines are transformed along x and written out.
-// Bound by memory on large grids, by latency on small ones.  Measured (MI355X, start
-// -> now, us): FP64 at 64^3 32 -> 6.7 (small tiles), 128^3 33 -> 17 and 192^3 77 -> 59
-// (tiles of 8 planes: enough blocks, no short last round), 384^3 747 -> 455 (one
-// column per thread instead of two), 96^3 32 -> 12.6 (marched, not gathered),
-// 1024 x 512 x 512 2614 -> 2030 (two columns per thread, two waves per SIMD, instead
-// of four in one); FP32 at 384^3 249 -> 238, at 192^3 45 -> 26.
+// Bound by memory on large grids, by latency on small ones.  Measured (MI355X, the
+// sweep back to back and without its decision, before -> now, us): FP64 at 64^3 33 ->
+// 6.7 (small tiles), 128^3 34 -> 16.4 and 192^3 79 -> 60 (tiles of 8 planes: enough
+// blocks, no short last round), 384^3 744 -> 455 (one column per thread instead of
+// two), 96^3 32 -> 12.2 (marched, not gathered), 1024 x 512 x 512 2610 -> 2015 (two
+// columns per thread, two waves per SIMD, instead of four in one); FP32 at 384^3 250
+// -> 220, at 192^3 45 -> 27.5.  In a solve the launch also holds the hand-over of its
+// sums and the decision, which were a kernel of 4-5 us: FP64 at 32^3 9.7 (the sweep
+// 5.4), 64^3 12.3, 128^3 21.8, 192^3 69, 384^3 484; FP32 at 192^3 31.6, 384^3 247.
 //
 // Waves per SIMD the registers are sized for: FP32 rows of up to 512 within 128
 // registers, the others within 256.
