@@ -63,6 +63,7 @@ struct ColShape {
         return L * (int)sizeof(cpx<T>) < 128 ? xcd_block(b, nb) : b;
     }
     static constexpr int MINW = NT > 512 ? NT / 256 : FIT < 1 ? 1 : FIT > 2 ? 2 : FIT;
+    static constexpr bool EARLY = N < 256 || L == narrow_lines<T, N>();  // see loads_issued
 };
 
 template <typename T, int N, int L>
@@ -73,6 +74,8 @@ k_dht_cols(GridArgs g, const Slot* __restrict__ slots, Tables tb, int stage, int
     __shared__ cpx<T> lds[L * F::LS];
     __shared__ cpx<T> tw[N];
     const Slot& s = slots[blockIdx.y];
+    if constexpr (!ColShape<T, N, L>::EARLY)
+        if (mode == 0 && IterView<T>::skip(s.st, stage)) return;
     TwiddleLoad<T, N, NT> twl;
     twl.load(twiddles<T>(tb, 1));
     POIS_GLOBAL T* Wc = mode == 0 ? IterView<T>(s).W : (POIS_GLOBAL T*)gptr(s.W);  // complex-indexed
@@ -93,8 +96,10 @@ k_dht_cols(GridArgs g, const Slot* __restrict__ slots, Tables tb, int stage, int
     unsigned grp = ColShape<T, N, L>::first_group(blockIdx.x, gridDim.x), base;
     bool valid;
     load(grp, valid, base);
-    loads_issued();
-    if (mode == 0 && IterView<T>::skip(s.st, stage)) return;
+    if constexpr (ColShape<T, N, L>::EARLY) {
+        loads_issued();
+        if (mode == 0 && IterView<T>::skip(s.st, stage)) return;
+    }
     twl.store(tw);
     __syncthreads();  // twiddles
     while (true) {
@@ -131,6 +136,7 @@ k_dht_cols_regs(GridArgs g, const Slot* __restrict__ slots, Tables tb, int stage
     __shared__ cpx<T> lds[C::L * C::LS];
     __shared__ cpx<T> tw[N];
     const Slot& s = slots[blockIdx.y];
+    if (mode == 0 && IterView<T>::skip(s.st, stage)) return;
     TwiddleLoad<T, N, C::NT> twl;
     twl.load(twiddles<T>(tb, 1));
     POIS_GLOBAL T* Wc = mode == 0 ? IterView<T>(s).W : (POIS_GLOBAL T*)gptr(s.W);  // complex-indexed
@@ -157,8 +163,6 @@ k_dht_cols_regs(GridArgs g, const Slot* __restrict__ slots, Tables tb, int stage
     unsigned grp = blockIdx.x, base;
     bool valid;
     load(grp, valid, base);
-    loads_issued();
-    if (mode == 0 && IterView<T>::skip(s.st, stage)) return;
     twl.store(tw);
     // the line stays in registers; LDS only for the transpose of the
     // transform and the exchange of the (k, N-k) partners, which stays
@@ -427,6 +431,8 @@ k_dht_z_solve(GridArgs g, const Slot* __restrict__ slots, Tables tb, int stage, 
     __shared__ cpx<T> tw[N];
     __shared__ T lzs[N / 2 + 1];  // the scaled z symbol, even in k (see k_dht_z_solve_regs)
     const Slot& s = slots[blockIdx.y];
+    if constexpr (!ColShape<T, N, L>::EARLY)
+        if (mode == 0 && IterView<T>::skip(s.st, stage)) return;
     TwiddleLoad<T, N, NT> twl;
     twl.load(twiddles<T>(tb, 2));
     POIS_GLOBAL T* Wc = mode == 0 ? IterView<T>(s).W : (POIS_GLOBAL T*)gptr(s.W);  // complex-indexed
@@ -450,8 +456,10 @@ k_dht_z_solve(GridArgs g, const Slot* __restrict__ slots, Tables tb, int stage, 
     unsigned grp = ColShape<T, N, L>::first_group(blockIdx.x, gridDim.x), base;
     bool valid;
     load(grp, valid, base);
-    loads_issued();
-    if (mode == 0 && IterView<T>::skip(s.st, stage)) return;
+    if constexpr (ColShape<T, N, L>::EARLY) {
+        loads_issued();
+        if (mode == 0 && IterView<T>::skip(s.st, stage)) return;
+    }
     twl.store(tw);
     for (int e = threadIdx.x; e <= N / 2; e += NT) lzs[e] = symbol<T>(tb, 2)[e] * sc;
     __syncthreads();  // twiddles, symbol

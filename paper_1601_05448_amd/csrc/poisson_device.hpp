@@ -615,14 +615,15 @@ __device__ __forceinline__ const float* symbol<float>(const Tables& t, int axis)
     return axis == 0 ? t.lamx32 : axis == 1 ? t.lamy32 : t.lamz32;
 }
 
-// A line sweep's first loads (the twiddles, the first line group) are issued before
-// it looks at the solve's state, so that a launch waits for memory once and not
-// twice (0.1-0.2 us of 3.3-4.0 on a 32^3 grid).  The stencil sweeps look at the state
-// first: early loads gained nothing there.  So does the register z sweep of lines of
-// 256 and 512 (k_dht_z_solve_regs), which runs only where its line groups fill the
-// chip and its launch takes 50 us and more.  A launch with nothing to do reads a
-// little and returns.  The fence only keeps the compiler from moving the loads below
-// the branch.
+// Where a line sweep looks at the solve's state: after it has issued its first loads
+// (the twiddles, the first line group), so that a launch waits for memory once and not
+// twice (0.1-0.2 us of 3.3-4.0 on a 32^3 grid; 128^3 and 192^3 solves 1% faster), or,
+// on lines of 256 and more in blocks that fill the chip, before them: there one memory
+// latency is little beside the launch, and launches with nothing to do, which would
+// read what all the resident blocks hold, are cheaper (a solve that starts solved: 346
+// -> 301 us at 256^3, 378 -> 320 on 512 x 512 x 64).  The stencil sweeps look first:
+// early loads gained nothing there.  The fence only keeps the compiler from moving the
+// loads below the branch.
 __device__ __forceinline__ void loads_issued() { asm volatile("" ::: "memory"); }
 
 // N twiddles on their way to LDS: NT threads load them, and store them later.

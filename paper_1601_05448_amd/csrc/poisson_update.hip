@@ -30,6 +30,7 @@ struct UpdateShape {
     static constexpr int NT = !WIDE || WHOLE == 192 ? WHOLE : N == 512 && !BCX ? 512 : 256;
     static constexpr int L = NT / F::TT;
     static constexpr int IT = L * N / NT;  // values per thread
+    static constexpr bool EARLY = N < 256 || !WIDE;  // see loads_issued
     static_assert(NT % 64 == 0 && L * F::TT == NT && (NT % N == 0 || N % NT == 0), "whole lines and rows");
 };
 
@@ -42,6 +43,8 @@ k_dhtx_update(GridArgs g, const Slot* __restrict__ slots, Tables tb, int stage, 
     __shared__ cpx<T> lds[L * F::LS];
     __shared__ cpx<T> tw[N];
     const Slot& s = slots[blockIdx.y];
+    if constexpr (!U::EARLY)
+        if (mode != 1 && IterView<T>::skip(s.st, stage)) return;
     const cpx<T>* twc = dct_twiddles<T>(tb);
     TwiddleLoad<T, N, NT> twl;
     twl.load(twiddles<T>(tb, 0));
@@ -78,8 +81,10 @@ k_dhtx_update(GridArgs g, const Slot* __restrict__ slots, Tables tb, int stage, 
     };
     unsigned grp = blockIdx.x;
     load_w(grp);
-    loads_issued();
-    if (mode != 1 && IterView<T>::skip(s.st, stage)) return;
+    if constexpr (U::EARLY) {
+        loads_issued();
+        if (mode != 1 && IterView<T>::skip(s.st, stage)) return;
+    }
     // the update of the last inner evaluation is applied here: the next inner
     // residual sweep may run (no other block of this launch reads the flag)
     if constexpr (sizeof(T) == 4)
