@@ -491,7 +491,10 @@ hipError_t launch_outer_residual(const GridArgs& g, const Geometry& geo, const T
 
 hipError_t launch_outer_update(const GridArgs& g, const Geometry& geo, const Slot* slots, int nslots,
                                hipStream_t s) {
-    k_outer_update<<<dim3(std::min(geo.blocks_pt, 2048), nslots), kPtThreads, 0, s>>>(g, slots);
+    // every block arrives at its solve's counters: in a batch no more than fill the chip
+    // (40 solves of 64^3: 68 -> 40 us)
+    const int nb = std::min(std::min(geo.blocks_pt, 2048), std::max(32, 8192 / nslots));
+    k_outer_update<<<dim3(nb, nslots), kPtThreads, 0, s>>>(g, slots);
     return hipGetLastError();
 }
 

@@ -30,12 +30,17 @@ __device__ __forceinline__ bool p1_idle(const Slot& s, int decide) {
     return false;
 }
 
+// Sums of a unit: r^2, bt^2, and in FP64 p and p^2.
+template <typename T>
+constexpr int kSums = sizeof(T) == 8 ? 4 : 2;
+
 // The end of an evaluation: the last block adds the units' sums and decides.
 template <typename T, int NT>
 __device__ __forceinline__ void p1_decide(const GridArgs& g, const Slot& s, unsigned units, int decide, double* red) {
     if (!decide || !last_block(s)) return;
-    double sums[4];
-    sum_units<NT, 4>(s.partial, units, sums, red);
+    constexpr int K = kSums<T>;
+    double sums[K];
+    sum_units<NT, K>(s.partial, units, sums, red);
     if (threadIdx.x != 0) return;
     if constexpr (sizeof(T) == 4) decide_inner(s.st, sums, kMaxInnerPerStep);
     else decide_fp64(g, s.st, sums);
@@ -50,7 +55,7 @@ k_resid_dhtx(GridArgs g, const Slot* __restrict__ slots, Tables tb, int decide) 
     using C = LineCfg<T, N>;
     __shared__ cpx<T> lds[C::L * C::LS];
     __shared__ cpx<T> tw[N];
-    __shared__ double red[(C::NT / 64) * 4];
+    __shared__ double red[(C::NT / 64) * kSums<T>];
     const Slot& s = slots[blockIdx.y];
     if (MODE == 0 && p1_idle<T>(s, decide)) return;
     const cpx<T>* twg = twiddles<T>(tb, 0);
@@ -61,7 +66,7 @@ k_resid_dhtx(GridArgs g, const Slot* __restrict__ slots, Tables tb, int decide) 
     const unsigned ngroups = (nlines + C::L - 1) / C::L;
     const IterView<T> v(s);
     POIS_GLOBAL T* W = (MODE == 0) ? v.W : (POIS_GLOBAL T*)gptr(s.W);
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};  // sum r^2, sum bt^2, sum p, sum p^2
+    double acc[kSums<T>] = {};
 
     // element `it` of this thread in a group: line (tid + it NT) / N, column (tid + it NT) % N
     auto fetch = [&](unsigned grp, int it, PairIn<T>& in) {
@@ -88,8 +93,10 @@ k_resid_dhtx(GridArgs g, const Slot* __restrict__ slots, Tables tb, int decide) 
             qv = {o.a.w * o.a.r, o.b.w * o.b.r};
             acc[0] += (double)o.a.r * o.a.r + (double)o.b.r * o.b.r;
             acc[1] += (double)o.a.bt * o.a.bt + (double)o.b.bt * o.b.bt;
-            acc[2] += (double)o.a.pc + (double)o.b.pc;
-            acc[3] += (double)o.a.pc * o.a.pc + (double)o.b.pc * o.b.pc;
+            if constexpr (sizeof(T) == 8) {
+                acc[2] += (double)o.a.pc + (double)o.b.pc;
+                acc[3] += (double)o.a.pc * o.a.pc + (double)o.b.pc * o.b.pc;
+            }
         }
         lds[l * C::LS + C::pos(x_slot(i, N, g.bcx))] = qv;
     };
@@ -132,7 +139,7 @@ k_resid_dhtx(GridArgs g, const Slot* __restrict__ slots, Tables tb, int decide) 
                 W[(2 * P + 1) * N + k] = h.y;
             }
         }
-        if (MODE == 0) put_unit_sums<C::NT, 4>(acc, red, s.partial + (unsigned long long)grp * kPartialStride);
+        if (MODE == 0) put_unit_sums<C::NT, kSums<T>>(acc, red, s.partial + (unsigned long long)grp * kPartialStride);
         grp += gridDim.x;
         if (grp >= ngroups) break;
         __syncthreads();  // the next group overwrites the lines
@@ -175,7 +182,7 @@ k_resid_dhtx_z(GridArgs g, const Slot* __restrict__ slots, Tables tb, int nflush
     constexpr int KF = RF::KF;
     __shared__ cpx<T> lds[Z::SUB * KF * LF::LS];
     __shared__ cpx<T> tw[N];
-    __shared__ double red[(Z::NT / 64) * 4];
+    __shared__ double red[(Z::NT / 64) * kSums<T>];
     __shared__ PlaneRows<T> xb[2 * Z::SUB * Z::XV];  // x neighbours, double-buffered by step parity
     const Slot& s = slots[blockIdx.y];
     if (p1_idle<T>(s, decide)) return;
@@ -197,7 +204,7 @@ k_resid_dhtx_z(GridArgs g, const Slot* __restrict__ slots, Tables tb, int nflush
     zm.nz = nz;
     zm.sz = (unsigned)N * (unsigned)g.ny;
     zm.lane = (int)(threadIdx.x & 63);
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};  // sum r^2, sum bt^2, sum p, sum p^2
+    double acc[kSums<T>] = {};
 
     for (unsigned tile = xcd_block(blockIdx.x, gridDim.x); tile < ntiles; tile += gridDim.x) {
         const unsigned tj = tile % ngj, tk = tile / ngj;
@@ -302,7 +309,7 @@ k_resid_dhtx_z(GridArgs g, const Slot* __restrict__ slots, Tables tb, int nflush
             });
             __syncthreads();  // the next flush overwrites the lines
         }
-        put_unit_sums<Z::NT, 4>(acc, red, s.partial + (unsigned long long)tile * kPartialStride);
+        put_unit_sums<Z::NT, kSums<T>>(acc, red, s.partial + (unsigned long long)tile * kPartialStride);
     }
     p1_decide<T, Z::NT>(g, s, ntiles, decide, red);
 }
@@ -319,7 +326,7 @@ k_resid_dhtx_s(GridArgs g, const Slot* __restrict__ slots, Tables tb, int decide
     static_assert(Z::CPT == 1, "one column per thread");
     __shared__ cpx<T> lds[Z::SUB * KF * LF::LS];
     __shared__ cpx<T> tw[N];
-    __shared__ double red[(Z::NT / 64) * 4];
+    __shared__ double red[(Z::NT / 64) * kSums<T>];
     __shared__ PlaneRows<T> xb[KF * Z::SUB * Z::XV];
     const Slot& s = slots[blockIdx.y];
     if (p1_idle<T>(s, decide)) return;
@@ -341,7 +348,7 @@ k_resid_dhtx_s(GridArgs g, const Slot* __restrict__ slots, Tables tb, int decide
     zm.nz = nz;
     zm.sz = (unsigned)N * (unsigned)g.ny;
     zm.lane = (int)(threadIdx.x & 63);
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    double acc[kSums<T>] = {};
     for (unsigned tile = xcd_block(blockIdx.x, gridDim.x); tile < ntiles; tile += gridDim.x) {
         const unsigned tj = tile % ngj, tk = tile / ngj;
         const unsigned jp = tj * Z::SUB + sidx;
@@ -399,7 +406,7 @@ k_resid_dhtx_s(GridArgs g, const Slot* __restrict__ slots, Tables tb, int decide
                 v.W[at + zm.rb] = h.y;
             }
         });
-        put_unit_sums<Z::NT, 4>(acc, red, s.partial + (unsigned long long)tile * kPartialStride);  // ends on a barrier
+        put_unit_sums<Z::NT, kSums<T>>(acc, red, s.partial + (unsigned long long)tile * kPartialStride);  // ends on a barrier
     }
     p1_decide<T, Z::NT>(g, s, ntiles, decide, red);
 }

@@ -8,15 +8,18 @@
 namespace pois {
 
 // Thread layout of a tile for rows of length N (16 and longer): SUB strips (row
-// pairs) of MT threads, each thread CPT columns of its strip's pair, MT apart.
-// wide: about 256 threads; else the fewest strips that fill whole waves.
+// pairs) of MT threads, each thread CPT columns of its strip's pair, MT apart.  About
+// 256 threads; small tiles (not WIDE) of rows longer than 64 the fewest strips that fill
+// whole waves.  (On shorter rows one wave alone had a quarter of its lanes busy in the
+// transform of its two planes' lines, which a batch of solves pays for: 64 served FP32
+// solves of 64^3 4.79 ms, with four waves of strips, whose lines fill one of them, 4.48.)
 template <int N, bool WIDE>
 struct RowTile {
     static_assert(N >= 16, "shorter rows are gathered");
     static constexpr int CPT = N > 512 ? 2 : 1;
     static constexpr int MT = N / CPT;
     static constexpr int WHOLE = N % 64 == 0 ? 1 : N % 32 == 0 ? 2 : N % 16 == 0 ? 4 : 8;  // strips of whole waves
-    static constexpr int SUB = !WIDE || MT >= 192 ? WHOLE : N == 96 ? 2 : N % 3 == 0 ? 192 / N : 256 / N;
+    static constexpr int SUB = MT >= 192 || (!WIDE && N > 64) ? WHOLE : N == 96 ? 2 : N % 3 == 0 ? 192 / N : 256 / N;
     static constexpr int NT = SUB * MT;
     static constexpr bool DPP = N % 64 == 0;                  // x neighbours from the neighbouring lanes
     static constexpr int XV = DPP ? (N / 64) * 2 : N;         // exchanged PlaneRows per strip and plane

@@ -27,11 +27,10 @@ CASES = [
 ]
 
 
-def _small_tiles(shape):
-    """(how many small tiles the grid has, threads of one)"""
+def _small_tile_threads(shape):
+    """Threads of all the small tiles: one per column of a row pair and two planes."""
     nz, ny, nx = shape
-    strips = 1 if nx % 64 == 0 else 2 if nx % 32 == 0 else 4 if nx % 16 == 0 else 8  # row pairs of whole waves
-    return math.ceil(ny // 2 / strips) * math.ceil(nz / 2), strips * nx
+    return math.ceil(nz / 2) * (ny // 2) * nx
 
 
 @pytest.mark.parametrize("shape,walls,coef,weight", CASES)
@@ -40,8 +39,7 @@ def test_marching_residual(shape, walls, coef, weight, precision):
     import torch
 
     announce("marching residual", shape, walls, coef, weight, precision)
-    tiles, threads = _small_tiles(shape)
-    assert tiles > torch.cuda.get_device_properties(0).multi_processor_count * (2048 // threads)
+    assert _small_tile_threads(shape) > torch.cuda.get_device_properties(0).multi_processor_count * 2048
     nz, ny, nx = shape
     h = TWO_PI / min(shape)
     prob = inputs.small_problem(shape=shape, lengths=(nx * h, ny * h, nz * h), ratio=3.0, kmax=2.0)
