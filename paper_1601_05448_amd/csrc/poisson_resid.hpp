@@ -158,13 +158,13 @@ using NormSum = std::conditional_t<N % 64 == 0, float, double>;
 // planes the tile's lines are transformed along x and written out.
 // Bound by memory on large grids, by latency on small ones.  Measured (MI355X, the
 // sweep back to back and without its decision, before -> now, us): FP64 at 64^3 33 ->
-// 6.7 (small tiles), 128^3 34 -> 16.4 and 192^3 79 -> 60 (tiles of 8 planes: enough
-// blocks, no short last round), 384^3 744 -> 455 (one column per thread instead of
-// two), 96^3 32 -> 12.2 (marched, not gathered), 1024 x 512 x 512 2610 -> 2015 (two
+// 6.3 (small tiles), 128^3 34 -> 16.2 and 192^3 79 -> 61 (tiles of 8 planes: enough
+// blocks, no short last round), 384^3 744 -> 456 (one column per thread instead of
+// two), 96^3 32 -> 12.3 (marched, not gathered), 1024 x 512 x 512 2610 -> 2020 (two
 // columns per thread, two waves per SIMD, instead of four in one); FP32 at 384^3 250
-// -> 220, at 192^3 45 -> 27.5.  In a solve the launch also holds the hand-over of its
-// sums and the decision, which were a kernel of 4-5 us: FP64 at 32^3 9.7 (the sweep
-// 5.4), 64^3 12.3, 128^3 21.8, 192^3 69, 384^3 484; FP32 at 192^3 31.6, 384^3 247.
+// -> 215, at 192^3 45 -> 27.  In a solve the launch also holds the hand-over of its
+// sums and the decision, which were a kernel of 4-5 us: FP64 at 32^3 9.5 (the sweep
+// 5.9), 64^3 11.9, 128^3 21.4, 192^3 68, 384^3 484; FP32 at 192^3 29.8, 384^3 237.
 //
 // Waves per SIMD the registers are sized for: FP32 rows of up to 512 within 128
 // registers, the others within 256.

@@ -76,7 +76,7 @@ struct RowFlush {
 
 // Flushes of `kf` planes per wide tile (so that the two halo planes are shared by
 // more planes), up to `most` planes, that give the fewest plane steps over the
-// rounds of tiles the resident blocks take: 192^3 in FP64 takes 8 planes (60 us),
+// rounds of tiles the resident blocks take: 192^3 in FP64 takes 8 planes (61 us),
 // not 32 (80 us: 512 of 576 tiles in a first round).
 inline int pick_flushes(int kf, int most, unsigned strips, unsigned nz, unsigned resident) {
     const unsigned all = (nz + (unsigned)kf - 1) / (unsigned)kf;
@@ -98,7 +98,7 @@ constexpr int kSmallPlanes = 2;
 
 // Whether a sweep takes its small tiles (all loads at once): where they all fit on
 // the chip at once, so that the sweep lasts one block's chain (the sweep alone, 64^3
-// in FP64: 6.7 us, marching 11.0; 96^3, more than one round: 17.5 against 12.2).
+// in FP64: 6.3 us, marching 11.0; 96^3, more than one round: 17.5 against 12.3).
 inline bool small_tiles_fit(unsigned tiles, unsigned resident) { return tiles <= resident; }
 
 }  // namespace pois
