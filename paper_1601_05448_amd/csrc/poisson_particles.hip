@@ -23,6 +23,7 @@
 #include <utility>
 
 #include "poisson_device.hpp"
+#include "poisson_particle_tiles.hpp"
 
 namespace pois {
 
@@ -303,24 +304,6 @@ k_part_pieces(PartGeom pg, int np, const double* __restrict__ pos, const double*
     }
 }
 
-// The tiles of k_part_cells: `rows` rows of one plane, tiles_y of them per plane.
-// Where their rows begin in the list of runs is kept in 2 tiles_y edges per plane, in
-// the order of their rows: row 0; rows j0 - 1 and j0 of every later tile; row ny - 1
-// (the row below row 0).  After the last plane's comes the end of the list.
-struct TileGeom {
-    int nx, ny, rows, tiles_y;
-    unsigned tiles, group;  // all tiles, neighbouring tiles of a block
-    // edges up to and with the row of the cell
-    __host__ __device__ unsigned edges_to(unsigned cell) const {
-        const unsigned row = cell / (unsigned)nx, k = row / (unsigned)ny;
-        const int j = (int)(row - k * (unsigned)ny);
-        const int above = (j + 1) / rows;
-        return k * 2u * (unsigned)tiles_y + 1u + (unsigned)(above < tiles_y ? above : tiles_y - 1) +
-               (unsigned)(j / rows) + (j + 1 == ny ? 1u : 0u);
-    }
-    __host__ __device__ unsigned edges() const { return 2u * tiles; }
-};
-
 // edge[from, to) = value of every lane: by the lane where they are few, by the whole
 // wave, lane after lane, where they are many (few particles on a large grid).  Every
 // lane of the wave calls it.
@@ -380,8 +363,10 @@ k_part_runs(int np, const uint2* __restrict__ pair, double* __restrict__ psum, c
     at += (unsigned)__popcll(started & (lane == 0 ? 0ull : ~0ull >> (64 - lane)));
     const unsigned here = tg.edges_to(k);
     put_edges(edge, starts && s > 0 ? tg.edges_to(prev) : 0u, starts ? here : 0u, (int)at);
-    const bool last = s + 1 == np;
-    put_edges(edge, last ? here : 0u, last ? tg.edges() + 1u : 0u, (int)at + (starts ? 1 : 0));
+    if (blockIdx.x + 1 == gridDim.x) {
+        const bool last = s + 1 == np;
+        put_edges(edge, last ? here : 0u, last ? tg.edges() + 1u : 0u, (int)at + (starts ? 1 : 0));
+    }
     if (!starts) return;
     run[at] = make_uint2(k, (unsigned)s);
     long long nxt = (s / kPiece + 1) * kPiece;
@@ -433,16 +418,9 @@ k_part_runs(int np, const uint2* __restrict__ pair, double* __restrict__ psum, c
 // by class / now, us: 10^6 on 512^3 uniform 732 / 432, one plane 490 / 470, 16 rows 500 /
 // 430, a ball of 16^3 cells 490 / 398, one cell 53500 / 22100; 2 10^6 on 256^3 639 / 306,
 // 2000 on 32^3 152 / 75.
-constexpr unsigned kSpanMax = 32;  // tiles of a block at most: one thread per bound (of eight)
 // runs of a thread at a time (10^6 uniform particles on 64 x 512 x 512, x first: 213 us;
 // with four 235)
 constexpr int kRuns = 2;
-
-// Tile m of block b of nb, whose groups are `group` tiles.
-__host__ __device__ __forceinline__ unsigned block_tile(unsigned m, unsigned group, unsigned b, unsigned nb) {
-    const unsigned g = m / group;
-    return (g * nb + b) * group + (m - g * group);
-}
 
 __global__ void __launch_bounds__(kPartThreads)
 k_part_cells(PartGeom pg, TileGeom tg, const uint2* __restrict__ run, const int* __restrict__ edge,
@@ -451,26 +429,29 @@ k_part_cells(PartGeom pg, TileGeom tg, const uint2* __restrict__ run, const int*
     static_assert(8 * kSpanMax == kPartThreads, "one thread per bound");
     extern __shared__ double acc[];
     __shared__ int bound[kSpanMax][2][4];  // [tile][plane k - 1, k]: its rows' first run and end; row ny - 1's
+    __shared__ int2 place[kSpanMax];       // its plane and first row, plane -1 after the block's last tile
     const int nx = pg.nx, ny = pg.ny, nz = pg.nz, rows = tg.rows, t = (int)threadIdx.x;
     const unsigned tiles_y = (unsigned)tg.tiles_y, tiles = tg.tiles;
     const int flag = bad[0];
     if (const unsigned tile = block_tile((unsigned)t >> 3, tg.group, blockIdx.x, gridDim.x); tile < tiles) {
         const unsigned k = tile / tiles_y, jt = tile - k * tiles_y;
         const unsigned kp = (t & 4) ? k : k == 0 ? (unsigned)nz - 1 : k - 1;
+        if ((t & 7) == 0) place[t >> 3] = make_int2((int)k, (int)jt * rows);
         const int which = t & 3;  // row max(j0 - 1, 0); row j1; row ny - 1; the plane's end
         const unsigned e = which == 0 ? (jt == 0 ? 0u : 2 * jt - 1)
                            : which == 1 ? 2 * jt + 2
                                         : 2 * tiles_y - (which == 2 ? 1u : 0u);
         bound[t >> 3][(t >> 2) & 1][which] = edge[kp * 2 * tiles_y + e];
+    } else if ((t & 7) == 0) {
+        place[t >> 3].x = -1;
     }
     if (flag) return;  // a bad position: the output stays as it is
     __syncthreads();
     const int pl = __builtin_amdgcn_readfirstlane(t / kHalf);  // the plane whose runs this wave takes
     const int wave0 = __builtin_amdgcn_readfirstlane(t & (kHalf - 64)), lane = t & 63;
     for (unsigned m = 0; m < kSpanMax; ++m) {
-        const unsigned tile = block_tile(m, tg.group, blockIdx.x, gridDim.x);
-        if (tile >= tiles) break;
-        const int k = (int)(tile / tiles_y), j0 = (int)(tile - (unsigned)k * tiles_y) * rows;
+        const int k = __builtin_amdgcn_readfirstlane(place[m].x), j0 = __builtin_amdgcn_readfirstlane(place[m].y);
+        if (k < 0) break;
         const int j1 = min(j0 + rows, ny), cells = (j1 - j0) * nx;
         const unsigned row0 = (unsigned)(pl ? k : k == 0 ? nz - 1 : k - 1) * (unsigned)ny;
         for (int c = t; c < cells; c += kPartThreads) acc[c] = 0.0;
@@ -504,7 +485,7 @@ k_part_cells(PartGeom pg, TileGeom tg, const uint2* __restrict__ run, const int*
                 for (int r = 0; r < R; ++r) {
                     c0[r] = c1[r] = -1;
                     if (at0 + r * kHalf < end) {
-                        const unsigned row = rn[r].x / (unsigned)nx;
+                        const unsigned row = tg.by_nx(rn[r].x);
                         const int i = (int)(rn[r].x - row * (unsigned)nx), j = (int)(row - row0);
                         const bool in = at0 + r * kHalf + lane < end;
                         dx[r] = i + 1 == nx ? -i : 1;
@@ -541,34 +522,6 @@ k_part_cells(PartGeom pg, TileGeom tg, const uint2* __restrict__ run, const int*
         double* o = out + ((size_t)k * ny + j0) * nx;
         for (int c = t; c < cells; c += kPartThreads) o[c] = acc[c];
     }
-}
-
-// Rows of a tile of k_part_cells: eight, or what fits 32 KB of LDS (four blocks per
-// CU), fewer where that leaves the chip without four blocks per CU.  More rows share
-// the row below the tile (10^6 particles on 512^3: 510, 432 and 436 us with 2, 4 and 8
-// rows; on 64 x 512 x 512, x first: 350, 270 and 220; 3 10^5 on 768 x 192 x 384: 221 with
-// 2 and 205 with 5).  Then as many tiles per block as leave eight blocks per CU.
-static int tile_rows(const GridArgs& g) {
-    int rows = std::max(1, std::min({g.ny, 8, 4096 / g.nx}));
-    while (rows > 1 && (long long)g.nz * ((g.ny + rows - 1) / rows) < 1024) rows = (rows + 1) / 2;
-    return rows;
-}
-
-// Neighbouring tiles of a block, up to kTileGroup of them: neighbours are written a
-// little faster, tiles far apart share out a crowd (10^6 particles on 512^3, uniform /
-// in one plane: 1 of 16 tiles 444 / 443 us, 2 432 / 469, 4 431 / 525, 8 437 / 686).
-constexpr unsigned kTileGroup = 2;
-
-static TileGeom tile_geom(const GridArgs& g) {
-    const int rows = tile_rows(g), tiles_y = (g.ny + rows - 1) / rows;
-    const unsigned tiles = (unsigned)g.nz * (unsigned)tiles_y;
-    return TileGeom{g.nx, g.ny, rows, tiles_y, tiles, std::clamp(tiles / 2048u, 1u, kTileGroup)};
-}
-
-static unsigned tile_blocks(const TileGeom& tg) {
-    const unsigned groups = (tg.tiles + tg.group - 1) / tg.group;
-    const unsigned span = std::clamp(groups / 2048u, 1u, kSpanMax / kTileGroup);
-    return (groups + span - 1) / span;
 }
 
 __global__ void __launch_bounds__(kPartThreads)
