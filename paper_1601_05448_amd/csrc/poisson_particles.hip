@@ -395,9 +395,9 @@ k_part_runs(int np, const uint2* __restrict__ pair, double* __restrict__ psum, c
     for (int c = 0; c < 8; ++c) psum[8 * (size_t)s + c] = acc[c];
 }
 
-// The deposit itself: a block owns up to kSpanMax tiles of `rows` rows of one plane,
-// a few neighbours and then others far away, one after the other, and gathers the corner sums that fall on each
-// tile [j0, j1) x nx in LDS.  They come from the runs of plane k - 1 (their upper half,
+// The deposit itself: a block owns up to kSpanMax tiles of `rows` rows of one plane, a
+// few neighbours and then others far away, one after the other, and gathers the corner
+// sums that fall on each tile [j0, j1) x nx in LDS.  They come from the runs of plane k - 1 (their upper half,
 // e = 1) and of plane k (e = 0), rows j0 - 1 to j1 - 1: two contiguous ranges of the
 // list of runs, and two more for the row below row 0, ny - 1.  Half of the block's
 // threads take each plane's range, kRuns runs each at a time.  Runs are distinct cells,
@@ -409,13 +409,13 @@ k_part_runs(int np, const uint2* __restrict__ pair, double* __restrict__ psum, c
 // LDS.  Filling the grid with zeros and adding the runs in eight passes (one per
 // parity class of the run's cell) moved whole lines both ways for 8-byte updates:
 // 172 us of filling beside the sort and 267 us of passes after it, for 10^6 particles
-// on 512^3, now 265 us in all (4.1 TB/s of the grid's 1.07 GB).
+// on 512^3, now 252-265 us in all (4.1-4.3 TB/s of the grid's 1.07 GB).
 // A tile's work is bounded by its cells, however many particles they hold, because
 // it walks runs, and particles that crowd some planes or rows crowd tiles of many
 // blocks, because most of a block's tiles lie far apart.  (Walking the particles, in
-// tiles that were all neighbours, was 7 us faster on uniform particles and took 3870
+// tiles that were all neighbours, was 10 us faster on uniform particles and took 3870
 // us for 10^6 of them in one plane of 512^3, 6850 in 16 rows of it.)  Deposits, passes
-// by class / now, us: 10^6 on 512^3 uniform 732 / 432, one plane 490 / 470, 16 rows 500 /
+// by class / now, us: 10^6 on 512^3 uniform 732 / 427, one plane 490 / 470, 16 rows 500 /
 // 430, a ball of 16^3 cells 490 / 398, one cell 53500 / 22100; 2 10^6 on 256^3 639 / 306,
 // 2000 on 32^3 152 / 75.
 // runs of a thread at a time (10^6 uniform particles on 64 x 512 x 512, x first: 213 us;
